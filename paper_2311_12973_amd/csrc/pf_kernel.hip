@@ -25,6 +25,7 @@
 #include <utility>
 
 #include "block_ops.h"
+#include "fast_fp64.h"
 #include "pf_kernel.h"
 
 namespace smc2 {
@@ -45,6 +46,8 @@ template <typename real> struct MConst {
     double l1p_ei;  // log1p(-min(p_ei, 1-p_ei)), log1p(-min(p_ir, 1-p_ir)) in FP64
     double l1p_ir;
     double r;       // negative-binomial dispersion
+    double lr1;     // log sqrt(1/2) - log r
+    bool r_ok;      // r in [2^-30, 2^30]: nb_cost applies
     int32_t x0[12]; // initial compartment counts
     double ar, sq, sr, m0, s0;  // linear-Gaussian: x_t = ar x_{t-1} + sq e_t, y_t = x_t + sr d_t,
                                 // x_0 = m0 + s0 e_0
@@ -105,6 +108,10 @@ __device__ __forceinline__ void model_setup(const PFArgs& a, const double* th, M
     }
     mc.l1p_ei = l1p_of<real>(mc.p_ei);
     mc.l1p_ir = l1p_of<real>(mc.p_ir);
+    if (MODEL != MODEL_SIR) {
+        mc.r_ok = uniform_bool(mc.r >= 0x1p-30 && mc.r <= 0x1p30);
+        mc.lr1 = uniform_f64(-0x1.62e42fefa39efp-2 - log(mc.r));
+    }
     if (MODEL == MODEL_AGE) {
         // every thread computed the same values: held in scalar registers, they leave
         // the vector registers to the draws
@@ -190,21 +197,81 @@ template <int MODEL> struct DrawGroups {
     static constexpr int G = MODEL == MODEL_SIR ? 2 : (MODEL == MODEL_SEIR ? 3 : (MODEL == MODEL_AGE ? 4 : 1));
 };
 
+// obs_part as a call, for the values that nb_obs cannot round: out of line, its registers
+// do not weigh on the day's loop.
+__device__ __attribute__((noinline)) double nb_part_call(int32_t y, int32_t mu, double r)
+{
+    return obs_part<OBS_NB_INC>(y, mu, r);
+}
+
+// The particle's part of log g under the negative binomial, summed over the NG series in
+// order, rounded to `real`. FP32: from nb_cost where that rounds safely (the same bits),
+// else from the library's logarithms. obs_part is 277 vector instructions a series, the
+// two log1p 135 each; this is 52 (age-structured SEIR, 2048 filters x 2048 x 365:
+// two iterations 377.6 -> 340.0 ms; SEIR, 1000 filters x 1000 x 150: 8.68 -> 7.79 ms).
+template <typename real, int NG>
+__device__ __forceinline__ real nb_obs(const MConst<real>& mc, const int32_t* yt, const int32_t (&mu)[NG])
+{
+    if constexpr (sizeof(real) == 4) {
+        float v = 0.0f;
+        bool ok = mc.r_ok;
+        if (ok) {
+            double s = 0.0;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const double y = (double)yt[g];
+                const double c = nb_cost(y, (double)(mu[g] > 0 ? mu[g] : 1), mc.r, mc.lr1);
+                s = s + (mu[g] > 0 ? c : (yt[g] == 0 ? 0.0 : (double)INFINITY));
+            }
+            ok = round_safe(s, v);
+        }
+        if (!ok) {
+            double lg = 0.0;
+#pragma nounroll
+            for (int g = 0; g < NG; ++g) {
+                int32_t m = mu[0];
+#pragma unroll
+                for (int h = 1; h < NG; ++h) m = g == h ? mu[h] : m;
+                lg = lg + nb_part_call(yt[g], m, mc.r);
+            }
+            v = -(float)lg;
+        }
+        return -v;
+    } else {
+        double lg = 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) lg = lg + obs_part<OBS_NB_INC>(yt[g], mu[g], mc.r);
+        return lg;
+    }
+}
+
+// The particle's part of log g for a model with one series, rounded to `real`.
+template <typename real, int OBS>
+__device__ __forceinline__ real obs_one(const MConst<real>& mc, const int32_t* yt, int32_t cnt)
+{
+    if constexpr (OBS == OBS_NB_INC) {
+        const int32_t mu[1] = {cnt};
+        return nb_obs<real, 1>(mc, yt, mu);
+    } else {
+        return (real)obs_part<OBS>(yt[0], cnt, mc.r);
+    }
+}
+
 // One day of the chain-binomial model for particle j, whose counts live in LDS
 // (st[c * cap + j]); flows drawn from the previous day's state. Draw index b:
 // SIR (S->I, I->R) = (0, 1); SEIR (S->E, E->I, I->R) = (0, 1, 2); age-structured
 // group g: 3g, 3g+1, 3g+2 (the draw index equals the index of the compartment the
 // flow leaves). One copy of the sampler per model: the draws of a day run in a
-// loop. Returns the per-particle part of log g(y_t | x_t) in FP64. With SCORE it adds
+// loop. Returns the per-particle part of log g(y_t | x_t), its FP64 value rounded to `real`. With SCORE it adds
 // the day's complete-data score to the particle's: per flow d log Bin / d h times
 // d h / d theta (I / N_pop for beta, 1 for sigma and gamma), d log g / d r, and for the
 // linear-Gaussian model the derivatives of its two Gaussian densities. With ptotal > 0
 // each draw group first sets the wave's issue priority (progress_priority, step pbase +
 // group of ptotal).
 template <typename real, int MODEL, int OBS, bool SCORE = false>
-__device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* st, int cap, int j,
-                                               DrawStream ds, const int32_t* yt, const ScoreDay& sd = ScoreDay{},
-                                               int pbase = 0, int ptotal = 0)
+__device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st, int32_t* flows, int cap, int j,
+                                             DrawStream ds, const int32_t* yt, const ScoreDay& sd = ScoreDay{},
+                                             int pbase = 0, int ptotal = 0)
 {
     if constexpr (MODEL == MODEL_LG) {
         // x_t = ar x_{t-1} + sq e_t; log g = -z^2 / 2 with z = (y_t - x_t) / sr (the
@@ -221,7 +288,7 @@ __device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* 
             lds_add_f64(sd.sw + 2 * cap, cap, j, (e * e - 1.0) / mc.sq);
             lds_add_f64(sd.sw + 4 * cap, cap, j, (z * z - 1.0) / mc.sr);
         }
-        return -0.5 * z * z;
+        return (real)(-0.5 * z * z);
     }
     if (MODEL == MODEL_SIR) {
         const int32_t S = st[j], I = st[cap + j];
@@ -242,7 +309,7 @@ __device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* 
             lds_add_f64(sd.sw, cap, j, flow_score<real>(S, p_si, nsi) * ((double)I / sd.n_pop));
             lds_add_f64(sd.sw + 2 * cap, cap, j, flow_score<real>(I, mc.p_ir, nir));
         }
-        return obs_part<OBS>(yt[0], OBS == OBS_POIS_PREV ? I1 : nsi, mc.r);
+        return obs_one<real, OBS>(mc, yt, OBS == OBS_POIS_PREV ? I1 : nsi);
     } else if (MODEL == MODEL_SEIR) {
         const int32_t S = st[j], E = st[cap + j], I = st[2 * cap + j];
         const real p_se = leave_prob<real>(mc.cinf * (real)I);
@@ -273,7 +340,7 @@ __device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* 
                 lds_add_f64(sd.sw + 8 * cap, cap, j, (sd.dpsi - log1p(mu / r)) + (mu - (double)yt[0]) / (r + mu));
             }
         }
-        return obs_part<OBS>(yt[0], OBS == OBS_POIS_PREV ? I1 : nei, mc.r);
+        return obs_one<real, OBS>(mc, yt, OBS == OBS_POIS_PREV ? I1 : nei);
     } else {
         // forces of infection from the previous day's infected counts
         real pse0, pse1, pse2, pse3;
@@ -290,7 +357,6 @@ __device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* 
             pse2 = leave_prob<real>(acc[2]);
             pse3 = leave_prob<real>(acc[3]);
         }
-        double lg = 0.0;
 #pragma nounroll
         for (int g = 0; g < 4; ++g) {
             if (ptotal > 0) progress_priority(pbase + g, ptotal);
@@ -312,9 +378,14 @@ __device__ __forceinline__ double particle_day(const MConst<real>& mc, int32_t* 
             st[(3 * g) * cap + j] = S - nse;
             st[(3 * g + 1) * cap + j] = E + nse - nei;
             st[(3 * g + 2) * cap + j] = I1;
-            lg = lg + obs_part<OBS>(yt[g], OBS == OBS_POIS_PREV ? I1 : nei, mc.r);
+            flows[g * cap + j] = nei;
         }
-        return lg;
+        // the observation terms after the draws, four independent chains at once; the
+        // day's new cases wait in the weight and gather buffers, free while drawing
+        int32_t mu[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) mu[g] = flows[g * cap + j];
+        return nb_obs<real, 4>(mc, yt, mu);
     }
 }
 
@@ -580,12 +651,13 @@ __device__ void draws_pooled(const MConst<real>& mc, const int32_t* st, int32_t*
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// The day's count update and the per-particle part of log g from the drawn flows. With
+// The day's count update and the per-particle part of log g (rounded to `real`) from the
+// drawn flows. With
 // SCORE it adds the day's complete-data score terms from the day-start counts and the
 // flows, the same FP64 values in the same order as the per-draw schedule's particle_day.
 template <typename real, int MODEL, int OBS, bool SCORE = false>
-__device__ __forceinline__ double particle_update(const MConst<real>& mc, int32_t* st, const int32_t* flows,
-                                                  int cap, int j, const int32_t* yt, const ScoreDay& sd = ScoreDay{})
+__device__ __forceinline__ real particle_update(const MConst<real>& mc, int32_t* st, const int32_t* flows,
+                                                int cap, int j, const int32_t* yt, const ScoreDay& sd = ScoreDay{})
 {
     if (MODEL == MODEL_SIR) {
         const int32_t nsi = flows[j], nir = flows[cap + j];
@@ -598,7 +670,7 @@ __device__ __forceinline__ double particle_update(const MConst<real>& mc, int32_
             lds_add_f64(sd.sw, cap, j, flow_score<real>(S, p_si, nsi) * ((double)I / sd.n_pop));
             lds_add_f64(sd.sw + 2 * cap, cap, j, flow_score<real>(I, mc.p_ir, nir));
         }
-        return obs_part<OBS>(yt[0], OBS == OBS_POIS_PREV ? I1 : nsi, mc.r);
+        return obs_one<real, OBS>(mc, yt, OBS == OBS_POIS_PREV ? I1 : nsi);
     } else {
         const int32_t nse = flows[j], nei = flows[cap + j], nir = flows[2 * cap + j];
         const int32_t S = st[j], E = st[cap + j], I = st[2 * cap + j];
@@ -616,7 +688,7 @@ __device__ __forceinline__ double particle_update(const MConst<real>& mc, int32_
                 lds_add_f64(sd.sw + 8 * cap, cap, j, (sd.dpsi - log1p(mu / r)) + (mu - (double)yt[0]) / (r + mu));
             }
         }
-        return obs_part<OBS>(yt[0], OBS == OBS_POIS_PREV ? I1 : nei, mc.r);
+        return obs_one<real, OBS>(mc, yt, OBS == OBS_POIS_PREV ? I1 : nei);
     }
 }
 
@@ -765,8 +837,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             __syncthreads();  // any wave may have drawn any particle's flows
             if (tid == 0) wg_next = 0;  // for the next day (read again only after further barriers)
             for (int j = tid; j < nx; j += nthr) {
-                const double lg = particle_update<real, MODEL, OBS, SCORE>(mc, st, flows, cap, j, yt, sd);
-                const real av = lw[j] + (real)lg;
+                const real av = lw[j] + particle_update<real, MODEL, OBS, SCORE>(mc, st, flows, cap, j, yt, sd);
                 lw[j] = av;
                 amax = av > amax ? av : amax;
             }
@@ -778,10 +849,10 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             constexpr int G = DrawGroups<MODEL>::G;
             const int ptotal = (SCORE || a.prio_scale > 0.f) ? 0 : (cap / nthr) * G;
             for (int j = tid, pass = 0; j < nx; j += nthr, ++pass) {
-                const double lg = particle_day<real, MODEL, OBS, SCORE>(
-                    mc, st, cap, j, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1}, yt, sd, pass * G,
+                const real lg = particle_day<real, MODEL, OBS, SCORE>(
+                    mc, st, flows, cap, j, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1}, yt, sd, pass * G,
                     ptotal);
-                const real av = lw[j] + (real)lg;
+                const real av = lw[j] + lg;
                 lw[j] = av;
                 amax = av > amax ? av : amax;
             }

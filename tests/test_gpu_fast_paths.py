@@ -1,0 +1,52 @@
+"""GPU parity of the short evaluations of the filter kernel, at the edges of their ranges.
+
+The FP32 filters take an FP64 value rounded to FP32 from a short evaluation where every
+nearby number rounds alike, and from the library function otherwise, so each must equal
+the reference's filter wherever the two meet: at the limits of the short form's range and
+outside it.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2311_12973_amd as G
+from paper_2311_12973_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _same_filters(w, theta, y, nx, prec=G.PREC_FP32, **kw):
+    """Every day's counts of every filter and its resampling decisions equal the reference's.
+    A weight or a probability that rounds differently moves an ancestor or a draw, and from
+    then on the counts. (The likelihoods also hold the day's constant, whose lgamma
+    differences cancel at large r; the counts do not.)"""
+    print(w["name"], kw, flush=True)
+    _, _, rs, st = G.pf_trace_state(w, theta, y, nx, seed=9, k=2, precision=prec, **kw)
+    cfg = O.config_from_workload(w, prec=prec)
+    for i, th in enumerate(theta):
+        _, _, rs_ref, st_ref = O.pf_trace_state(cfg, th, y, nx, 9, i, 2)
+        assert np.array_equal(rs[i], rs_ref), i
+        assert np.array_equal(st[i], st_ref), i
+
+
+@pytest.mark.parametrize("r", [2.0**-31, 2.0**-30, 1e-3, 1.0, 7.25, 2.0**30, 2.0**31])
+@pytest.mark.parametrize("model", ["seir", "age_seir"])
+def test_negative_binomial_term_over_the_dispersion(model, r):
+    """The observation term for dispersions inside, at and outside [2^-30, 2^30], with
+    days of no observed and no new cases (mu = 0) in a small population and mu on both
+    sides of r."""
+    w = W.preset(model)
+    w.update(n_pop=400.0, T=30)
+    truth = np.array(w["truth"])
+    truth[3] = 0.02
+    if model == "seir":
+        w["fixed"] = [r]
+    else:
+        truth[4] = r
+    y = W.simulate(w["model"], w["obs"], w["n_pop"], np.where(np.arange(len(truth)) == 4, 10.0, truth), w["T"], 3,
+                   [10.0] if model == "seir" else w["fixed"])
+    assert (y == 0).any() and (y > 3).any()
+    theta = np.tile(truth, (16, 1))
+    theta[:, :3] *= np.exp(np.random.default_rng(4).normal(0, 0.1, (16, 3)))
+    for schedule in ([G.SCHED_PER_DRAW, G.SCHED_POOLED] if model == "seir" else [G.SCHED_AUTO]):
+        _same_filters(w, theta, y, 130, schedule=schedule)
