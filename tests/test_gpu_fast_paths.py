@@ -50,3 +50,32 @@ def test_negative_binomial_term_over_the_dispersion(model, r):
     theta[:, :3] *= np.exp(np.random.default_rng(4).normal(0, 0.1, (16, 3)))
     for schedule in ([G.SCHED_PER_DRAW, G.SCHED_POOLED] if model == "seir" else [G.SCHED_AUTO]):
         _same_filters(w, theta, y, 130, schedule=schedule)
+
+
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+@pytest.mark.parametrize("region", ["small", "boundary", "wide"])
+def test_rejection_sampler_final_test_edges(prec, region):
+    """Draws whose final acceptance test sits at the edges of its FP32 form: n p just above
+    10 (candidates below 4 take tabulated corrections, |d| / (k + 1) beyond 1/8 the
+    logarithms), n on both sides of 2^23 (above, the FP64 test), and everything between.
+    Half a million draws each, identical integers."""
+    rng = np.random.default_rng(41)
+    M = 1 << 19
+    if region == "small":
+        n = np.floor(10 ** rng.uniform(1.31, 3.0, M)).astype(np.int64)
+        p = np.minimum(10.0 ** rng.uniform(1.0, 1.6, M) / n, 0.5)
+        p[: M // 8] = 0.5
+    elif region == "boundary":
+        n = rng.integers((1 << 23) - 2048, (1 << 23) + 2048, M)
+        p = 10 ** rng.uniform(-5.9, np.log10(0.9), M)
+    else:
+        n = np.floor(10 ** rng.uniform(1.5, 7.0, M)).astype(np.int64)
+        p = 10 ** (np.log10(10.0 / n) + (np.log10(0.97) - np.log10(10.0 / n)) * rng.random(M))
+    n = n.astype(np.int32)
+    if prec == G.PREC_FP32:
+        p = p.astype(np.float32).astype(np.float64)
+    print("final test", region, prec, flush=True)
+    got = G.binomial_batch(prec, n, p, seed=5, i=2, k=3, t=7, b=1)
+    want = O.binomial_many(prec, n, p, 5, i=2, k=3, t=7, b=1)
+    bad = np.flatnonzero(got != want)
+    assert len(bad) == 0, [(int(n[j]), float(p[j]), int(got[j]), int(want[j])) for j in bad[:8]]
