@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fast_fp64.h"
+
 namespace smc2 {
 
 enum : uint32_t { S_PF_PROP = 1u, S_PF_RS = 2u, S_PRIOR = 3u, S_RW = 4u, S_OUTER_RS = 5u, S_MLP_INIT = 6u,
@@ -137,14 +139,34 @@ template <> __device__ __forceinline__ double rcp_int<double>(int m) { return c_
 // f_0 = (1-p)^n, f_{k+1} = f_k ((n-k) r) / (k+1), r = p/(1-p); stops at the first k
 // whose running sum reaches u, when adding a term no longer changes the sum, or
 // at k = min(n, 127).
-// l1p = log1p(-p) in FP64 (hoisted by callers whose p is fixed per filter).
+// l1p = log1p(-p) in FP64 (hoisted by callers whose p is fixed per filter), NaN when the
+// caller does not have it.
+//
+// f_0 by the library functions: 42 vector instructions, and 135 more for log1p.
+template <typename real> __device__ __forceinline__ real inversion_first(int32_t n, real p, double l1p)
+{
+    const double lq = (l1p == l1p) ? l1p : log1p(-(double)p);
+    return (real)exp((double)n * lq);
+}
+// FP32: 25 and 18 instructions (age-structured SEIR, 2048 filters x 2048 x 365, two
+// iterations: 325 -> 310 ms with leave_prob4)
+__device__ __forceinline__ float inversion_first_fast(int32_t n, float p, double l1p)
+{
+    const double lq = (l1p == l1p) ? l1p : log1m_half((double)p);
+    float f;
+    if (!round_safe(exp_neg((double)n * lq), f)) f = inversion_first<float>(n, p, l1p);
+    return f;
+}
+
 template <typename real>
 __device__ __forceinline__ int32_t binom_inversion(int32_t n, real p, double l1p, uint32_t word)
 {
     const real u = (real)u24(word);
     const real q = (real)1 - p;
     const real r = rdiv<real>(p, q);
-    real f = (real)exp((double)n * l1p);
+    real f;
+    if constexpr (sizeof(real) == 4) f = inversion_first_fast(n, p, l1p);
+    else f = inversion_first<real>(n, p, l1p);
     real F = f;
     int32_t k = 0;
     const int32_t kcap = n < 127 ? n : 127;
@@ -435,18 +457,42 @@ __device__ __forceinline__ int32_t binomial(int32_t n, real p, const DrawStream&
     const real pp = flip ? (real)1 - p : p;
     int32_t k;
     if ((real)n * pp < (real)10) {
-        const double lq = (l1p == l1p) ? l1p : log1p(-(double)pp);
-        k = binom_inversion<real>(n, pp, lq, s.call(0u).x);
+        k = binom_inversion<real>(n, pp, l1p, s.call(0u).x);
     } else {
         k = binom_btrs<real>(n, pp, s);
     }
     return flip ? n - k : k;
 }
 
-// Probability 1 - exp(-x) of leaving a compartment within a day at hazard x.
-template <typename real> __device__ __forceinline__ real leave_prob(real x)
+// Probability 1 - exp(-x) of leaving a compartment within a day at hazard x: the FP64 value
+// rounded to `real`. FP32: from the short evaluation where that rounds safely (24 vector
+// instructions), else the library's expm1 (53; also for x outside [0, 16)).
+template <typename real> __device__ __forceinline__ real leave_prob(real x);
+template <> __device__ __forceinline__ double leave_prob<double>(double x) { return -expm1(-x); }
+template <> __device__ __forceinline__ float leave_prob<float>(float x)
 {
-    return (real)(-expm1(-(double)x));
+    float p;
+    const bool ok = round_safe(one_minus_exp_neg((double)x), p);
+    if (!(ok && x >= 0.0f && x < 16.0f)) p = (float)(-expm1(-(double)x));
+    return p;
+}
+// four at once, in one block: four independent chains hide each other's latency and share the
+// coefficients' scalar moves
+template <typename real> __device__ __forceinline__ void leave_prob4(const real (&x)[4], real (&p)[4])
+{
+    if constexpr (sizeof(real) == 4) {
+        bool ok = true;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            ok = (round_safe(one_minus_exp_neg((double)x[g]), p[g]) && x[g] >= 0.0f && x[g] < 16.0f) && ok;
+        if (!ok) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) p[g] = (float)(-expm1(-(double)x[g]));
+        }
+    } else {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) p[g] = leave_prob<real>(x[g]);
+    }
 }
 
 // ----------------------------------------------------------- observations (FP64)

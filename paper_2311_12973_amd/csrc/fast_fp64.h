@@ -26,6 +26,12 @@ __device__ __forceinline__ double fma_s(double a, double b, double c)
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
     return d;
 }
+__device__ __forceinline__ double fma_m(double a, double c, double b)  // a c + b
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %3, %2" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+}
 __device__ __forceinline__ double add_s(double a, double c)
 {
     double d;
@@ -60,6 +66,56 @@ __device__ __forceinline__ double atanh2_third(double s)
     p = fma_s(p, z, 0x1.5555555694e91p-1);
     p = fma_s(p, z, 0x1.ffffffffffdc7p+0);
     return s * p;
+}
+
+// expm1(r) for |r| <= 0.35: r times a polynomial of degree 8, the Chebyshev interpolant
+// (relative error below 2^-43.2)
+__device__ __forceinline__ double expm1_reduced(double r)
+{
+    double p = fma_s(r, 0x1.72cbc2d115ac0p-19, 0x1.a160af3a7fe30p-16);
+    p = fma_s(p, r, 0x1.a019aa4cb1c39p-13);
+    p = fma_s(p, r, 0x1.6c164950be7a3p-10);
+    p = fma_s(p, r, 0x1.1111111cf461cp-7);
+    p = fma_s(p, r, 0x1.555555760904bp-5);
+    p = fma_s(p, r, 0x1.555555555395fp-3);
+    p = fma_s(p, r, 0x1.fffffffff6629p-2);
+    p = fma(p, r, 1.0);
+    return r * p;
+}
+
+// 1 - exp(-x), 0 <= x < 16: exp(-x) = 2^k exp(r) with |r| <= log(2) / 2, so the value is
+// (1 - 2^k) - 2^k expm1(r); for k = 0 it is -expm1(r) and keeps its relative accuracy
+__device__ __forceinline__ double one_minus_exp_neg(double x)
+{
+    const double k = rint(mul_s(x, -0x1.71547652b82fep+0));
+    const double q = expm1_reduced(fma_m(k, -0x1.62e42fefa39efp-1, -x));
+    const double sc = __builtin_amdgcn_ldexp(1.0, (int)k);
+    return fma(-sc, q, 1.0 - sc);
+}
+
+// exp(t), -700 < t <= 0
+__device__ __forceinline__ double exp_neg(double t)
+{
+    const double k = rint(mul_s(t, 0x1.71547652b82fep+0));
+    const double q = expm1_reduced(fma_m(k, -0x1.62e42fefa39efp-1, t));
+    return __builtin_amdgcn_ldexp(1.0 + q, (int)k);
+}
+
+// log1p(-p), 0 < p <= 1/2: -2 atanh(p / (2 - p)), the argument within 1/3 (degree 8,
+// relative error below 2^-47 with the quotient's)
+__device__ __forceinline__ double log1m_half(double p)
+{
+    const double s = quot_fast(p, 2.0 - p);
+    const double z = s * s;
+    double a = fma_s(z, 0x1.802a101eedabfp-3, 0x1.e113009e29adap-4);
+    a = fma_s(a, z, 0x1.3ee359d54f9bep-3);
+    a = fma_s(a, z, 0x1.741ba33d08379p-3);
+    a = fma_s(a, z, 0x1.c71f002282a8cp-3);
+    a = fma_s(a, z, 0x1.2492420132b9cp-2);
+    a = fma_s(a, z, 0x1.999999ad7f31fp-2);
+    a = fma_s(a, z, 0x1.555555554ab02p-1);
+    a = fma_s(a, z, 0x1.0000000000007p+1);
+    return -(s * a);
 }
 
 // log(x) + c for x > 0 normal: x = f 2^e with f in [1/2, 1), log x = e log 2 + log sqrt(1/2)

@@ -25,7 +25,6 @@
 #include <utility>
 
 #include "block_ops.h"
-#include "fast_fp64.h"
 #include "pf_kernel.h"
 
 namespace smc2 {
@@ -352,10 +351,12 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
 #pragma unroll
                 for (int h = 0; h < 4; ++h) acc[g] = acc[g] + mc.cs[g][h] * (real)st[(3 * h + 2) * cap + j];
             }
-            pse0 = leave_prob<real>(acc[0]);
-            pse1 = leave_prob<real>(acc[1]);
-            pse2 = leave_prob<real>(acc[2]);
-            pse3 = leave_prob<real>(acc[3]);
+            real ps[4];
+            leave_prob4<real>(acc, ps);
+            pse0 = ps[0];
+            pse1 = ps[1];
+            pse2 = ps[2];
+            pse3 = ps[3];
         }
 #pragma nounroll
         for (int g = 0; g < 4; ++g) {
@@ -468,8 +469,7 @@ __device__ __forceinline__ bool item_begin(const MConst<real>& mc, const int32_t
     flip = p > (real)0.5;
     pp = flip ? (real)1 - p : p;
     if ((real)n * pp < (real)10) {
-        const double lq = (l1p == l1p) ? l1p : log1p(-(double)pp);
-        const int32_t k = binom_inversion<real>(n, pp, lq, ds.call(0u).x);
+        const int32_t k = binom_inversion<real>(n, pp, l1p, ds.call(0u).x);
         res = flip ? n - k : k;
         return true;
     }
@@ -750,7 +750,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
     constexpr bool POOLED = (SCHED == PF_SCHED_POOLED || SCHED == PF_SCHED_SCORE_POOLED) &&
                             (MODEL == MODEL_SIR || MODEL == MODEL_SEIR);
     constexpr int NS = SCORE ? ScoreDims<MODEL>::NS : 0;  // score columns (FP64, two words each)
-    const int g = a.items ? a.items[item] : item;
+    const int g = uniform_i32(a.items ? a.items[item] : item);
     const int tid = (int)threadIdx.x;
     const int nthr = (int)blockDim.x;
     if (a.active && !a.active[g]) {
@@ -763,9 +763,16 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
     }
     const int run_i = g / a.N;
     const uint32_t filt = (uint32_t)(g - run_i * a.N);
-    const RunDev run = a.runs[run_i];
+    // the same in every thread: read as scalars (loaded through an index from memory, they
+    // would sit in vector registers)
+    RunDev run = a.runs[run_i];
+    run.T = uniform_i32(run.T);
+    run.nx = uniform_i32(run.nx);
+    run.y_off = uniform_i32(run.y_off);
+    run.k0 = (uint32_t)uniform_i32((int32_t)run.k0);
+    run.k1 = (uint32_t)uniform_i32((int32_t)run.k1);
     const int T = run.T, nx = run.nx;
-    const uint32_t kit = a.k_dev ? (uint32_t)(*a.k_dev) : a.k_const;
+    const uint32_t kit = (uint32_t)uniform_i32(a.k_dev ? *a.k_dev : (int32_t)a.k_const);
     const int cap = ((nx + nthr - 1) / nthr) * nthr;
 
     extern __shared__ __align__(16) unsigned char smem[];

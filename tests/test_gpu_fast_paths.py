@@ -21,12 +21,14 @@ def _same_filters(w, theta, y, nx, prec=G.PREC_FP32, **kw):
     then on the counts. (The likelihoods also hold the day's constant, whose lgamma
     differences cancel at large r; the counts do not.)"""
     print(w["name"], kw, flush=True)
-    _, _, rs, st = G.pf_trace_state(w, theta, y, nx, seed=9, k=2, precision=prec, **kw)
+    _, inc, rs, st = G.pf_trace_state(w, theta, y, nx, seed=9, k=2, precision=prec, **kw)
     cfg = O.config_from_workload(w, prec=prec)
     for i, th in enumerate(theta):
-        _, _, rs_ref, st_ref = O.pf_trace_state(cfg, th, y, nx, 9, i, 2)
+        _, inc_ref, rs_ref, st_ref = O.pf_trace_state(cfg, th, y, nx, 9, i, 2)
         assert np.array_equal(rs[i], rs_ref), i
-        assert np.array_equal(st[i], st_ref), i
+        assert np.array_equal(inc[i] == -np.inf, inc_ref == -np.inf), i
+        days = int(np.argmax(inc[i] == -np.inf)) + 1 if (inc[i] == -np.inf).any() else len(y)  # its last day
+        assert np.array_equal(st[i][:days], st_ref[:days]), i
 
 
 @pytest.mark.parametrize("r", [2.0**-31, 2.0**-30, 1e-3, 1.0, 7.25, 2.0**30, 2.0**31])
@@ -79,3 +81,14 @@ def test_rejection_sampler_final_test_edges(prec, region):
     want = O.binomial_many(prec, n, p, 5, i=2, k=3, t=7, b=1)
     bad = np.flatnonzero(got != want)
     assert len(bad) == 0, [(int(n[j]), float(p[j]), int(got[j]), int(want[j])) for j in bad[:8]]
+
+
+@pytest.mark.parametrize("beta", [1e-9, 1e-3, 0.5, 15.9, 16.1, 1e3, 1e8])
+def test_leave_probability_over_the_hazard(beta):
+    """The probability 1 - exp(-x) for hazards from 1e-13 through both sides of 16, where
+    its short form ends, to where it is 1: flows by inversion, rejection and none."""
+    w = dict(W.preset("sir_fp64"), n_pop=1000.0, fixed=[400], T=6)
+    y = np.full((6, 1), 60, dtype=np.int32)
+    theta = np.tile([beta, 0.1], (8, 1)) * np.exp(np.random.default_rng(6).normal(0, 0.05, (8, 2)))
+    for schedule in (G.SCHED_PER_DRAW, G.SCHED_POOLED):
+        _same_filters(w, theta, y, 200, schedule=schedule)
