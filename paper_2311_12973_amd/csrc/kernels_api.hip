@@ -235,7 +235,8 @@ static int pf_run(const smc2_config* cfg, int32_t n_theta, const double* d_theta
     if (cfg->schedule < 0 || cfg->schedule > 2) return kfail(SMC2_E_ARG, "schedule must be 0, 1 or 2");
     const int want = cfg->schedule;
     const int block =
-        cfg->block ? cfg->block : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, want, score);
+        cfg->block ? cfg->block
+                   : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, want, score, n_theta);
     const int sched = pf_pick_schedule(cfg->model, cfg->precision, block, run->n_x, run->T, want, score);
     if (sched < 0) return kfail(SMC2_E_ARG, "the pooled schedule cannot run this model, n_x and T");
     const size_t lds = pf_lds_bytes(cfg->model, cfg->precision, block, run->n_x, run->T, sched);

@@ -71,8 +71,9 @@ size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched);
 // supported and it fits in LDS), with score = true its score-carrying form; -1 when
 // the pooled schedule was requested but cannot run, or the model has no score.
 int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requested, bool score = false);
-// Default workgroup size for a filter of this shape (64 .. 1024 threads).
-int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score = false);
+// Default workgroup size for a filter of this shape (64 .. 1024 threads), in a launch of
+// n_filters filters of that shape (0: many, or of several shapes).
+int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters);
 bool pf_supported(int model, int obs);
 // Raise the dynamic-LDS limit of the kernel when a launch needs more than 64 KiB.
 hipError_t pf_prepare(int prec, int model, int obs, int sched, size_t lds);

@@ -1052,8 +1052,38 @@ size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched)
     return bytes;
 }
 
-int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score)
+// A launch of at most 512 filters leaves wave slots free with the sizes below: each of the
+// 256 CUs holds one or two filters, four waves each. A filter is then bound by the latency of
+// its days, one after another, so it gets the waves that its share of the CU's 16 (four a
+// SIMD at 128 VGPRs) allows, up to a particle per thread: half of 16 for two filters a CU, all
+// for one. More threads than particles measured slower (16 SIR filters, N_x = 500, pooled:
+// 256 threads 0.54 ms, 512 0.46, 768 0.49, 1024 0.55), as did three filters a CU on more than
+// four waves each (their waves no longer divide over the SIMDs; 700 SEIR filters, N_x = 300:
+// 256 threads 1.67 ms, 320 2.37). Measured, old size -> this: 100 linear-Gaussian filters,
+// N_x = 257, 0.66 -> 0.60 ms; 512 SEIR filters, N_x = 500, 1.91 -> 1.63 ms and with scores
+// 2.41 -> 1.96; 200 age-structured filters, N_x = 700, 5.28 -> 4.34 ms.
+static int pf_few_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
 {
+    const int per_cu = n_filters <= 256 ? 1 : 2;
+    const int full = ((nx + 63) / 64) * 64;
+    const int most = full < 1024 / per_cu ? full : 1024 / per_cu;
+    // the widest that runs pooled, down to half of the most; else the most on the per-draw schedule
+    int widest = 0;
+    for (int b = most; 2 * b >= most && b >= 64; b -= 64) {
+        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
+        if (sc < 0 || pf_lds_bytes(model, prec, b, nx, T, sc) * per_cu > PF_LDS_MAX) continue;
+        if (widest == 0) widest = b;
+        if (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED) return b;
+    }
+    return widest;
+}
+
+int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
+{
+    if (n_filters > 0 && n_filters <= 512) {
+        const int b = pf_few_filters_block(model, prec, nx, T, requested_sched, score, n_filters);
+        if (b > 0) return b;
+    }
     // the workgroup size that keeps the most waves resident per CU (LDS allowing,
     // at most 16 at 128 VGPRs), preferring the pooled schedule by its measured gain
     const int full = ((nx + 63) / 64) * 64;

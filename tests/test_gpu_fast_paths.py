@@ -92,3 +92,19 @@ def test_leave_probability_over_the_hazard(beta):
     theta = np.tile([beta, 0.1], (8, 1)) * np.exp(np.random.default_rng(6).normal(0, 0.05, (8, 2)))
     for schedule in (G.SCHED_PER_DRAW, G.SCHED_POOLED):
         _same_filters(w, theta, y, 200, schedule=schedule)
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 512, 513])
+@pytest.mark.parametrize("preset,nx", [("sir_fp64", 1), ("sir_fp64", 65), ("seir", 300), ("seir", 4096),
+                                       ("lingauss", 1000), ("age_seir", 700), ("age_seir", 2048)])
+def test_few_filters_take_wider_workgroups_with_the_same_results(preset, nx, n):
+    """At most 256 and at most 512 filters run on wider workgroups than larger launches:
+    the same likelihoods to the last bit as on 128 threads."""
+    w = W.preset(preset)
+    w["T"] = 3
+    y = W.simulate(w["model"], w["obs"], w["n_pop"], w["truth"], 3, 5, w.get("fixed", ()), min_frac=0)
+    theta = np.array(w["truth"]) * np.exp(np.random.default_rng(n).normal(0, 0.05, (n, w["D"])))
+    print(preset, nx, n, flush=True)
+    a = G.pf_loglik(w, theta, y, nx, seed=3, k=1)
+    b = G.pf_loglik(w, theta, y, nx, seed=3, k=1, block=128)
+    assert np.array_equal(a, b)
