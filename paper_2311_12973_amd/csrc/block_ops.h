@@ -28,10 +28,27 @@ template <typename real> __device__ __forceinline__ real block_max(real v, RedLd
     v = wave_max(v);
     if (lane_id() == 0) slot[wave_id()] = v;
     __syncthreads();
+    // every wave reads the slots into its first lanes and reduces them there
     const int nw = (int)(blockDim.x >> 6);
-    real m = slot[0];
-    for (int w = 1; w < nw; ++w) m = slot[w] > m ? slot[w] : m;
-    return m;
+    const real m = slot[lane_id() < nw ? lane_id() : 0];
+    return uniform_real<real>(row_reduce(m, [](real x, real u) { return u > x ? u : x; }));
+}
+
+// Sums of two u64 values over the block, as scalars.
+__device__ __forceinline__ void block_sum_u64(uint64_t& a, uint64_t& b, RedLds* red)
+{
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if (lane_id() == 0) {
+        red->sum_a[wave_id()] = a;
+        red->sum_b[wave_id()] = b;
+    }
+    __syncthreads();
+    const int nw = (int)(blockDim.x >> 6), l = lane_id() < nw ? lane_id() : 0;
+    const auto add = [](uint64_t x, uint64_t u) { return x + u; };
+    const uint64_t sa = red->sum_a[l], sb = red->sum_b[l];
+    a = uniform_u64(row_reduce(lane_id() < nw ? sa : 0ull, add));
+    b = uniform_u64(row_reduce(lane_id() < nw ? sb : 0ull, add));
 }
 
 // Sums over the block of one double and two u64 values; fixed reduction order
@@ -58,6 +75,14 @@ __device__ __forceinline__ void block_sum3(double& s, uint64_t& a, uint64_t& b, 
     }
 }
 
+// lane `l`'s value (l uniform) as a scalar
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
 // Exclusive scan over the block (thread order); returns the exclusive prefix and
 // the block total.
 __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t& total, RedLds* red)
@@ -65,15 +90,14 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t& total,
     const uint64_t incl = wave_incl_scan(v);
     if (lane_id() == 63) red->scan[wave_id()] = incl;
     __syncthreads();
-    const int nw = (int)(blockDim.x >> 6), me = wave_id();
-    uint64_t off = 0, tot = 0;
-    for (int w = 0; w < nw; ++w) {
-        const uint64_t x = red->scan[w];
-        off += (w < me) ? x : 0ull;
-        tot += x;
-    }
-    total = tot;
-    return off + incl - v;
+    // every wave scans the slots in its first row: the total, and its own offset
+    const int nw = (int)(blockDim.x >> 6), me = uniform_i32(wave_id());
+    const uint64_t slot = red->scan[lane_id() < nw ? lane_id() : 0];
+    const uint64_t own = lane_id() < nw ? slot : 0ull;
+    const uint64_t to = row_incl_scan(own);
+    const uint64_t before = to - own;
+    total = lane_u64(to, 15);
+    return lane_u64(before, me) + incl - v;
 }
 
 // ESS < n/2 on the quantised weights q' = q >> 8: 2 (sum q')^2 < n sum q'^2, exact.

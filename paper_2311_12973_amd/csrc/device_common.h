@@ -549,33 +549,92 @@ template <> __device__ __forceinline__ double uniform_real<double>(double v) { r
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
 __device__ __forceinline__ int wave_id() { return (int)(threadIdx.x >> 6); }
 
+// Exchanges between the lanes of a wave, on the vector ALU. Through LDS (ds_bpermute, what a
+// shuffle compiles to) a step waits about 60 cycles on top of its issue; six of them per
+// reduction, and several reductions a day, set the pace of a small filter (the reductions,
+// scans and sums of a day below: 100 linear-Gaussian filters, N_x = 257, 100 days,
+// 586 -> 485 us; 1000 SEIR filters, N_x = 1000, 150 days, 7.50 -> 6.92 ms).
+// A 32-bit word from another lane by a data-parallel primitive (CTRL); lanes without a source,
+// and rows outside ROWS, get 0.
+template <int CTRL, int ROWS = 0xF> __device__ __forceinline__ uint32_t dpp_word(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, true);
+}
+template <int CTRL, int ROWS = 0xF, typename T> __device__ __forceinline__ T dpp(T v)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, dpp_word<CTRL, ROWS>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint64_t lo = dpp_word<CTRL, ROWS>((uint32_t)u), hi = dpp_word<CTRL, ROWS>((uint32_t)(u >> 32));
+        return __builtin_bit_cast(T, lo | (hi << 32));
+    }
+}
+// op of lane l's value and lane l ^ O's, O = 32 or 16: the swap of half waves (of odd and even
+// rows) leaves the pair's two values in two registers of both lanes
+template <int O, typename T, typename F> __device__ __forceinline__ T swap_step(T v, F op)
+{
+    const auto sw = [](uint32_t x, uint32_t& a, uint32_t& b) {
+        const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                               : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = r[0];
+        b = r[1];
+    };
+    uint32_t a0, b0;
+    if constexpr (sizeof(T) == 4) {
+        sw(__builtin_bit_cast(uint32_t, v), a0, b0);
+        return op(__builtin_bit_cast(T, a0), __builtin_bit_cast(T, b0));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        uint32_t a1, b1;
+        sw((uint32_t)u, a0, b0);
+        sw((uint32_t)(u >> 32), a1, b1);
+        return op(__builtin_bit_cast(T, (uint64_t)a0 | ((uint64_t)a1 << 32)),
+                  __builtin_bit_cast(T, (uint64_t)b0 | ((uint64_t)b1 << 32)));
+    }
+}
+// the butterfly steps 8, 4, 2, 1 within a row of 16 lanes. After step 8 the values repeat
+// every 8 lanes, so a rotation by 4 brings lane l ^ 4's value.
+template <typename T, typename F> __device__ __forceinline__ T row_reduce(T v, F op)
+{
+    v = op(v, dpp<0x128>(v));  // rotate by 8
+    v = op(v, dpp<0x124>(v));  // rotate by 4
+    v = op(v, dpp<0x4E>(v));   // quad lanes 2, 3, 0, 1
+    return op(v, dpp<0xB1>(v));  // quad lanes 1, 0, 3, 2
+}
+template <typename T, typename F> __device__ __forceinline__ T wave_reduce(T v, F op)
+{
+    return row_reduce(swap_step<16>(swap_step<32>(v, op), op), op);
+}
+
+// all 64 lanes active; the butterfly's order of additions (lanes 32, 16, 8, 4, 2, 1 apart)
 template <typename T> __device__ __forceinline__ T wave_max(T v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const T u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
-    return v;
+    return wave_reduce(v, [](T x, T u) { return u > x ? u : x; });
 }
-
 template <typename T> __device__ __forceinline__ T wave_sum(T v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return wave_reduce(v, [](T x, T u) { return x + u; });
+}
+
+// inclusive scan within a row of 16 lanes, and within a wave (all 64 lanes active)
+__device__ __forceinline__ uint64_t row_incl_scan(uint64_t v)
+{
+    v += dpp<0x111>(v);  // from 1, 2, 4, 8 lanes below in the row
+    v += dpp<0x112>(v);
+    v += dpp<0x114>(v);
+    v += dpp<0x118>(v);
+    return v;
+}
+__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v)
+{
+    v = row_incl_scan(v);
+    v += dpp<0x142, 0xA>(v);  // each odd row adds the last lane of the row below it
+    v += dpp<0x143, 0xC>(v);  // the upper half adds lane 31
     return v;
 }
 
-// inclusive scan within a wave
-__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v)
-{
-    const int l = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t u = __shfl_up(v, o, 64);
-        if (l >= o) v += u;
-    }
-    return v;
-}
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v) { return __builtin_bit_cast(uint64_t, uniform_f64(__builtin_bit_cast(double, v))); }
 
 }  // namespace smc2

@@ -826,11 +826,13 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
     if (tid == 0) wg_next = 0;
     __syncthreads();
 
+    // kept by the first wave: the likelihood, the last day's FP64 weight sum (the score's
+    // normaliser) and the log of the previous day's (N_x after a resampling)
     double ll = 0.0;
-    double sl_last = 0.0;  // the last day's FP64 weight sum (the score's normaliser)
+    double sl_last = 0.0;
     int days = T;  // days run: T, or the day every weight vanished
     const double log_nx = log((double)nx);
-    double log_prev = log_nx;  // log of the previous day's weight sum (N_x after a resampling)
+    double log_prev = log_nx;
     for (int t = 1; t <= T; ++t) {
         const uint32_t kt = (kit << 16) | (uint32_t)t;
         if (a.prio_scale > 0.f) wave_priority((float)(T - t + 1) * (float)nx * a.prio_scale);
@@ -870,7 +872,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
                 for (int c = 0; c < NC; ++c)
                     a.trace_state[(((size_t)g * T + (t - 1)) * NC + c) * nx + j] = st[c * cap + j];
         }
-        const real m = uniform_real<real>(block_max<real>(amax, red));
+        const real m = block_max<real>(amax, red);
         if (m == (real)-INFINITY) {
             ll = -INFINITY;
             days = t;
@@ -907,20 +909,23 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             const double cs = wave_sum(w);
             if (lane_id() == 0) red->chunk[step * nwv + wave_id()] = cs;
         }
-        double sl = 0.0;
-        block_sum3(sl, q1, q2, red);
-        sl = 0.0;
-        for (int c = 0; c < (cap >> 6); ++c) sl += red->chunk[c];
-        sl_last = sl;
-        const double lsl = log(sl);
-        const double inc = (((double)m + lsl) - log_prev) + cst[t - 1];
-        ll = ll + inc;
-        log_prev = lsl;
+        block_sum_u64(q1, q2, red);
         // 3. resample when ESS < N_x / 2 (never after the last observation)
         const bool rs = uniform_bool(t < T && (a.pf_always || ess_below_half(q1, q2, nx)));
-        if (a.trace_inc && first_wave()) {
-            a.trace_inc[(size_t)g * T + t - 1] = inc;
-            a.trace_rs[(size_t)g * T + t - 1] = rs ? 1 : 0;
+        // the first wave alone keeps the likelihood: the ordered sum and the logarithm are a
+        // chain of some 200 instructions that the other waves need not repeat or wait for
+        if (first_wave()) {
+            double sl = 0.0;
+            for (int c = 0; c < (cap >> 6); ++c) sl += red->chunk[c];
+            sl_last = sl;
+            const double lsl = log(sl);
+            const double inc = (((double)m + lsl) - log_prev) + cst[t - 1];
+            ll = ll + inc;
+            log_prev = rs ? log_nx : lsl;
+            if (a.trace_inc) {
+                a.trace_inc[(size_t)g * T + t - 1] = inc;
+                a.trace_rs[(size_t)g * T + t - 1] = rs ? 1 : 0;
+            }
         }
         if (rs) {
             const uint64_t Q = block_scan_lds(C, nx, red);
@@ -955,7 +960,6 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
                 }
             }
             for (int j = tid; j < nx; j += nthr) lw[j] = (real)0;
-            log_prev = log_nx;
             // the next day's draws read any particle's counts (the pooled schedule hands
             // out items workgroup-wide): every gathered count must be in place first
             __syncthreads();
@@ -968,10 +972,11 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
         // summed per 64-particle chunk and the chunks in order, like the weight sum. The
         // chunk slots still hold the last day's weight sums, which every thread has read
         // only once all have passed this barrier.
+        if (first_wave()) red->sum_d[0] = ll;
         __syncthreads();
         const double* wT = reinterpret_cast<const double*>(C);
         const int nwv = nthr >> 6;
-        const bool alive = uniform_bool(ll != -INFINITY);
+        const bool alive = uniform_bool(red->sum_d[0] != -INFINITY);
         for (int d = 0; d < a.D; ++d) {
             double num = 0.0;
             if (alive && d < NS) {
