@@ -204,23 +204,28 @@ template <typename real> __device__ __forceinline__ real inversion_first(int32_t
 }
 // FP32: 25 and 18 instructions (age-structured SEIR, 2048 filters x 2048 x 365, two
 // iterations: 325 -> 310 ms with leave_prob4)
-__device__ __forceinline__ float inversion_first_fast(int32_t n, float p, double l1p)
+// n = 1: the value is 1 - p, which for one FP32 p in four lies halfway between two FP32
+// values, where nothing short decides: the callers that hoist l1p hoist it too (f1)
+__device__ __forceinline__ float inversion_first_fast(int32_t n, float p, double l1p, float f1)
 {
     const double lq = (l1p == l1p) ? l1p : log1m_half((double)p);
     float f;
-    if (!round_safe(exp_neg((double)n * lq), f)) f = inversion_first<float>(n, p, l1p);
+    bool ok = round_safe(exp_neg((double)n * lq), f);
+    const bool one = (n == 1) & (l1p == l1p);
+    f = one ? f1 : f;
+    if (!(ok | one)) f = inversion_first<float>(n, p, l1p);
     return f;
 }
 
 template <typename real>
-__device__ __forceinline__ int32_t binom_inversion(int32_t n, real p, double l1p, uint32_t word)
+__device__ __forceinline__ int32_t binom_inversion(int32_t n, real p, double l1p, real f1, uint32_t word)
 {
     const real u = (real)u24(word);
     const real q = (real)1 - p;
     // in range: p below 2^-100 gives f_0 = 1 > u, whatever the ratio
     const real r = rdiv_inrange<real>(p, q);
     real f;
-    if constexpr (sizeof(real) == 4) f = inversion_first_fast(n, p, l1p);
+    if constexpr (sizeof(real) == 4) f = inversion_first_fast(n, p, l1p, f1);
     else f = inversion_first<real>(n, p, l1p);
     real F = f;
     int32_t k = 0;
@@ -336,29 +341,30 @@ __device__ __forceinline__ bool btrs_final(const BtrsConst<real>& c, int32_t n, 
 // The same test evaluated in FP32 with a bound on its distance from the FP64
 // evaluation above; returns 1 (accept), -1 (reject), or 0 when the FP32 value is
 // too close to the boundary to decide (then the FP64 test decides). Exact algebra
-// on the test: with m = floor((n+1)p), d = k - m, A = k+1, B = n-k+1 and
-// lfact(x) = (x+1/2) log(x+1) - (x+1) + log(2 pi)/2 + fc(x), the FP64 right-hand side is
-//   (m+1/2) log((m+1)/A) + (n-m+1/2) log((n-m+1)/B) + d log(p B / (q A))
-//     + fc(m) + fc(n-m) - fc(k) - fc(n-k),
-// whose first two terms are each about +-d and cancel. With x1 = -d/A, x2 = d/B,
-// log((m+1)/A) = log1p(x1) and log((n-m+1)/B) = log1p(x2); for |x| <= 1/8,
-// log1p(x) = x + x^2 log1p_curve(x), and when both are that small the two linear parts
-// add up to the cancellation-free d [(d - 1/2)/B + (d + 1/2)/A]. Larger |x| take the
-// logarithm of the ratio, which is then at least 0.11 in magnitude. In the third term
-// p B - q A = ((n+1)p - m) + p - d - 1 + ((1-p) - q) A (q is 1 - p rounded to the filter's
-// precision, as in the FP64 test) is formed without cancellation. Reciprocals and
-// base-2 logarithms are the hardware instructions (relative error below 2^-22 on
-// gfx950), so every piece carries a relative error of a few tens of FP32 units at
-// most and 2^-17 times the sum of the magnitudes bounds the FP32 error; for n < 2^23,
-// n 2^-41 bounds the FP64 evaluation's own error (terms of size n ln n, a few roundings
-// each: 2^-46 (n+1)(1 + log2(n+2))). A decision taken outside both bounds is the FP64
-// decision. Needs n < 2^23 (integers exact in FP32). For the FP64 filters the set-up
+// on the test: with m = floor((n+1)p), d = k - m, M = m+1, N = n-m+1, A = k+1 = M+d,
+// B = n-k+1 = N-d and lfact(x) = (x+1/2) log(x+1) - (x+1) + log(2 pi)/2 + fc(x), the FP64
+// right-hand side is
+//   -(A-1/2) log(A/M) - (B-1/2) log(B/N) + d log(pN/(qM)) + fc(m) + fc(n-m) - fc(k) - fc(n-k).
+// With u1 = d/M, u2 = -d/N and h(u) = (1+u) log(1+u) - u, A log(A/M) = M h(u1) + d and
+// B log(B/N) = N h(u2) - d: the linear parts cancel exactly and
+//   rhs = -M h(u1) - N h(u2) + log((A/M)(B/N))/2 + d L0 + fc(m) + fc(n-m) - fc(k) - fc(n-k),
+// L0 = log(pN/(qM)). Both h are non-negative; for |u| <= 1/8, h(u) = u^2 entropy_curve(u),
+// beyond it A log(A/M) - d (and B log(B/N) + d), whose cancelling parts of size |d| enter
+// the bound. L0 = log1p(y0), y0 = (pN - qM)/(qM), pN - qM = fr + p - 1 + ((1-p) - q) M with
+// fr = (n+1)p - m (q is 1 - p rounded to the filter's precision, as in the FP64 test; its
+// error is formed exactly). Reciprocals and base-2 logarithms are the hardware instructions
+// (relative error below 2^-22 on gfx950), so every piece carries a relative error of a few
+// tens of FP32 units at most and 2^-17 times the sum of the magnitudes bounds the FP32
+// error; for n < 2^23, n 2^-41 bounds the FP64 evaluation's own error (terms of size n ln n,
+// a few roundings each: 2^-46 (n+1)(1 + log2(n+2))). A decision taken outside both bounds is
+// the FP64 decision. Needs n < 2^23 (integers exact in FP32). For the FP64 filters the set-up
 // values and p enter rounded to FP32, one more unit each.
-// The test is bound by instruction issue, and a wave runs it whenever one lane needs it:
-// about 140 vector instructions for 200 with every term's general form, and for 735 of the
-// FP64 test, which the FP64 filters ran for every candidate (FP64 SIR sampler, 1024 filters
-// x 500 x 30, ten iterations: 10.3 -> 7.8 ms; FP32, 1000 SEIR filters x 1000 x 150: 7.79 ->
-// 7.47 ms; 50 age-structured filters x 1500 x 200: 15.2 -> 13.4 ms).
+// The test is bound by instruction issue, and a wave runs it whenever one lane needs it: 2.5
+// times a draw on the per-draw schedule, with 15% of its lanes. What depends on (n, p) alone
+// is therefore computed once a draw (BtrsFinal, 48 vector instructions), leaving about 80 a
+// test, against 735 for the FP64 test (FP64 SIR sampler, 1024 filters x 500 x 30, ten
+// iterations: 10.3 -> 7.8 ms; the age-structured sampler, 140 a test -> this: 287 -> 257 ms,
+// Langevin 12.1 -> 11.4 ms).
 static __constant__ float c_fc_tab[4] = {0.081061466795327f, 0.041340695955409f, 0.027677925684998f,
                                         0.020790672103766f};
 
@@ -381,52 +387,72 @@ __device__ __forceinline__ float log1p_curve(float x)
     return fmaf(h, x, -0.5f);
 }
 
+// ((1+u) log(1+u) - u) / u^2 for |u| <= 1/8: the Chebyshev interpolant of degree 4 (relative
+// error below 2^-23.2)
+__device__ __forceinline__ float entropy_curve(float u)
+{
+    float h = 0.03368553f;
+    h = fmaf(h, u, -0.05046931f);
+    h = fmaf(h, u, 0.08333196f);
+    h = fmaf(h, u, -0.16666482f);
+    return fmaf(h, u, 0.5f);
+}
+
+// What the FP32 final test needs of (n, p) alone
+struct BtrsFinal {
+    float rM, rN;   // 1 / (m+1), 1 / (n-m+1)
+    float L0;       // log(p (n-m+1) / (q (m+1)))
+    float fmn;      // fc(m) + fc(n-m)
+    float alpha;    // (2.83 + 5.1 / b) sqrt(n p q)
+    int32_t m;
+};
+
+template <typename real> __device__ __forceinline__ BtrsFinal btrs_final_setup(const BtrsConst<real>& c, int32_t n, real p)
+{
+    BtrsFinal s;
+    const real q = (real)1 - p;
+    const double mp = (double)(n + 1) * (double)p;  // FP32 p: exact
+    s.m = (int32_t)mp;
+    const float fr = (float)__builtin_amdgcn_fract(mp);
+    const float M = (float)(s.m + 1), N = (float)(n - s.m + 1);
+    s.rM = fast_rcp(M);
+    s.rN = fast_rcp(N);
+    const float pf = (float)p, qf = (float)q;
+    const float dq = (float)(((real)1 - q) - p);
+    const float y0 = fmaf(dq, M, (fr + pf) - 1.0f) * fast_rcp(qf * M);
+    s.L0 = fabsf(y0) <= 0.125f ? fmaf(y0 * y0, log1p_curve(y0), y0) : fast_ln(1.0f + y0);
+    s.fmn = btrs_fc(s.rM) + btrs_fc(s.rN);
+    s.alpha = (2.83f + 5.1f * fast_rcp((float)c.bb)) * (float)c.spq;
+    return s;
+}
+
 template <typename real>
-__device__ __forceinline__ int btrs_final_fast(const BtrsConst<real>& c, int32_t n, real p, int32_t k, uint32_t wu,
-                                               uint32_t wv)
+__device__ __forceinline__ int btrs_final_fast(const BtrsConst<real>& c, const BtrsFinal& s, int32_t n, int32_t k,
+                                               uint32_t wu, uint32_t wv)
 {
     if (n >= (1 << 23)) return 0;
     const float u = u24(wu) - 0.5f;
     const float v = u24(wv);
     const float us = 0.5f - fabsf(u);
-    const real q = (real)1 - p;
-    const double mp = (double)(n + 1) * (double)p;  // FP32 p: exact
-    const int32_t m = (int32_t)mp;
-    const float fr = (float)(mp - floor(mp));
-    const int32_t d = k - m;
-    const float df = (float)d;
+    const float df = (float)(k - s.m);
     const float A = (float)(k + 1), B = (float)(n - k + 1);
-    const float M = (float)(m + 1), N = (float)(n - m + 1);
-    const float rA = fast_rcp(A), rB = fast_rcp(B);
-    const float mh = M - 0.5f, nmh = N - 0.5f;
-    // (m+1/2) log((m+1)/A) + (n-m+1/2) log((n-m+1)/B)
-    const float x1 = -df * rA, x2 = df * rB;
-    const bool s1 = fabsf(x1) <= 0.125f, s2 = fabsf(x2) <= 0.125f;
-    const float g1 = (x1 * x1) * log1p_curve(x1), g2 = (x2 * x2) * log1p_curve(x2);
-    const float lin = (s1 && s2) ? df * ((df - 0.5f) * rB + (df + 0.5f) * rA)
-                                 : (s1 ? mh * x1 : 0.0f) + (s2 ? nmh * x2 : 0.0f);
-    const float b1 = mh * (s1 ? g1 : fast_ln(M * rA));
-    const float b2 = nmh * (s2 ? g2 : fast_ln(N * rB));
-    // d log(p B / (q A)), q = fl(1 - p) as in the FP64 test: p B - q A =
-    // (fr + p - (d + 1)) + ((1 - p) - q) A; both differences of the rounding are exact, and
-    // the first sum cancels only at d = 0, where the term is zero
-    const float pf = (float)p, qf = (float)q;
-    const float dq = (float)(((real)1 - q) - p);
-    const float rq = fast_rcp(qf * A);
-    const float y3 = fmaf(dq, A, (fr + pf) - (df + 1.0f)) * rq;
-    const float l3 = fabsf(y3) <= 0.125f ? fmaf(y3 * y3, log1p_curve(y3), y3) : fast_ln((pf * B) * rq);
-    const float t3 = df * l3;
-    float fk = btrs_fc(rA), fnk = btrs_fc(rB);
+    const float u1 = df * s.rM, u2 = -df * s.rN;
+    const float a1 = A * s.rM, b1 = B * s.rN;
+    const bool s1 = fabsf(u1) <= 0.125f, s2 = fabsf(u2) <= 0.125f;
+    const float h1 = s1 ? (df * u1) * entropy_curve(u1) : fmaf(A, fast_ln(a1), -df);
+    const float h2 = s2 ? (-df * u2) * entropy_curve(u2) : fmaf(B, fast_ln(b1), df);
+    const float hl = 0.5f * fast_ln(a1 * b1);
+    float fk = btrs_fc(fast_rcp(A)), fnk = btrs_fc(fast_rcp(B));
     if (k < 4) fk = c_fc_tab[k];
     if (n - k < 4) fnk = c_fc_tab[n - k];
-    const float f = (btrs_fc(fast_rcp(M)) + btrs_fc(fast_rcp(N))) - (fk + fnk);
+    const float f = s.fmn - (fk + fnk);
     // left-hand side log(v alpha / (aa / us^2 + bb))
-    const float alpha = (2.83f + 5.1f * fast_rcp((float)c.bb)) * (float)c.spq;
     const float den = fmaf((float)c.aa, fast_rcp(us * us), (float)c.bb);
-    const float lhs = fast_ln((v * alpha) * fast_rcp(den));
-    const float D = (((lin + b1) + b2) + t3 + f) - lhs;
-    const float E = fmaf((float)n, 0x1p-41f,
-                         0x1p-17f * ((((fabsf(lin) + fabsf(b1)) + fabsf(b2)) + fabsf(t3)) + (fabsf(lhs) + 1.0f)));
+    const float lhs = fast_ln((v * s.alpha) * fast_rcp(den));
+    const float hs = h1 + h2;
+    const float D = ((fmaf(df, s.L0, hl) - hs) + f) - lhs;
+    const float S = ((hs + (s1 && s2 ? 0.0f : fabsf(df))) + fabsf(df * s.L0)) + (fabsf(lhs) + 1.0f);
+    const float E = fmaf((float)n, 0x1p-41f, 0x1p-17f * S);
     return D > E ? 1 : (D < -E ? -1 : 0);
 }
 
@@ -446,7 +472,7 @@ template <typename real>
 __device__ __forceinline__ bool btrs_decide(const BtrsConst<real>& c, int32_t n, real p, int32_t k, uint32_t wu,
                                             uint32_t wv)
 {
-    const int f = btrs_final_fast<real>(c, n, p, k, wu, wv);
+    const int f = btrs_final_fast<real>(c, btrs_final_setup<real>(c, n, p), n, k, wu, wv);
     bool acc = f > 0;
     if (f == 0) acc = btrs_final_call<real>(c, n, p, k, wu, wv);
     return acc;
@@ -462,6 +488,7 @@ template <typename real>
 __device__ __forceinline__ int32_t binom_btrs(int32_t n, real p, const DrawStream& s)
 {
     const BtrsConst<real> c = btrs_setup<real>(n, p);
+    const BtrsFinal fs = btrs_final_setup<real>(c, n, p);
     W4 w{0u, 0u, 0u, 0u};
     for (int e = 0; e < 256; ++e) {
         if ((e & 1) == 0) w = s.call((uint32_t)(e >> 1));
@@ -474,7 +501,7 @@ __device__ __forceinline__ int32_t binom_btrs(int32_t n, real p, const DrawStrea
         // register holding k was reused inside the final test on the accepting path).
         bool acc = r == BTRS_ACCEPT;
         if (r == BTRS_FINAL) {
-            const int f = btrs_final_fast<real>(c, n, p, k, wu, wv);
+            const int f = btrs_final_fast<real>(c, fs, n, k, wu, wv);
             acc = f > 0;
             if (f == 0) acc = btrs_final_call<real>(c, n, p, k, wu, wv);
         }
@@ -483,9 +510,10 @@ __device__ __forceinline__ int32_t binom_btrs(int32_t n, real p, const DrawStrea
     return btrs_mode<real>(n, p);
 }
 
-// Binomial(n, p). l1p, when not NaN, is log1p(-min(p, 1-p)) precomputed in FP64.
+// Binomial(n, p). l1p, when not NaN, is log1p(-min(p, 1-p)) precomputed in FP64, and f1
+// its exponential rounded to `real`.
 template <typename real>
-__device__ __forceinline__ int32_t binomial(int32_t n, real p, const DrawStream& s, double l1p = NAN)
+__device__ __forceinline__ int32_t binomial(int32_t n, real p, const DrawStream& s, double l1p = NAN, real f1 = (real)0)
 {
     if (n <= 0 || !(p > (real)0)) return 0;
     if (p >= (real)1) return n;
@@ -493,7 +521,7 @@ __device__ __forceinline__ int32_t binomial(int32_t n, real p, const DrawStream&
     const real pp = flip ? (real)1 - p : p;
     int32_t k;
     if ((real)n * pp < (real)10) {
-        k = binom_inversion<real>(n, pp, l1p, s.call(0u).x);
+        k = binom_inversion<real>(n, pp, l1p, f1, s.call(0u).x);
     } else {
         k = binom_btrs<real>(n, pp, s);
     }
@@ -509,7 +537,7 @@ template <> __device__ __forceinline__ float leave_prob<float>(float x)
 {
     float p;
     const bool ok = round_safe(one_minus_exp_neg((double)x), p);
-    if (!(ok && x >= 0.0f && x < 16.0f)) p = (float)(-expm1(-(double)x));
+    if (!(ok & (x >= 0.0f) & (x < 16.0f))) p = (float)(-expm1(-(double)x));
     return p;
 }
 // four at once, in one block: four independent chains hide each other's latency and share the
@@ -517,10 +545,11 @@ template <> __device__ __forceinline__ float leave_prob<float>(float x)
 template <typename real> __device__ __forceinline__ void leave_prob4(const real (&x)[4], real (&p)[4])
 {
     if constexpr (sizeof(real) == 4) {
+        // bitwise: a logical and would branch between the chains
         bool ok = true;
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            ok = (round_safe(one_minus_exp_neg((double)x[g]), p[g]) && x[g] >= 0.0f && x[g] < 16.0f) && ok;
+            ok = ok & round_safe(one_minus_exp_neg((double)x[g]), p[g]) & (x[g] >= 0.0f) & (x[g] < 16.0f);
         if (!ok) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) p[g] = (float)(-expm1(-(double)x[g]));

@@ -44,6 +44,7 @@ template <typename real> struct MConst {
     real cs[4][4];  // beta s_g C_gh / N_h  (age-structured)
     double l1p_ei;  // log1p(-min(p_ei, 1-p_ei)), log1p(-min(p_ir, 1-p_ir)) in FP64
     double l1p_ir;
+    real f1_ei, f1_ir;  // their exponentials
     double r;       // negative-binomial dispersion
     double lr1;     // log sqrt(1/2) - log r
     bool r_ok;      // r in [2^-30, 2^30]: nb_cost applies
@@ -107,6 +108,8 @@ __device__ __forceinline__ void model_setup(const PFArgs& a, const double* th, M
     }
     mc.l1p_ei = l1p_of<real>(mc.p_ei);
     mc.l1p_ir = l1p_of<real>(mc.p_ir);
+    mc.f1_ei = uniform_real<real>((real)exp(mc.l1p_ei));
+    mc.f1_ir = uniform_real<real>((real)exp(mc.l1p_ir));
     if (MODEL != MODEL_SIR) {
         mc.r_ok = uniform_bool(mc.r >= 0x1p-30 && mc.r <= 0x1p30);
         mc.lr1 = uniform_f64(-0x1.62e42fefa39efp-2 - log(mc.r));
@@ -297,7 +300,8 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
         for (int b = 0; b < 2; ++b) {
             if (ptotal > 0) progress_priority(pbase + b, ptotal);
             ds.b = (uint32_t)b;
-            const int32_t v = binomial<real>(b == 0 ? S : I, b == 0 ? p_si : mc.p_ir, ds, b == 0 ? NAN : mc.l1p_ir);
+            const int32_t v = binomial<real>(b == 0 ? S : I, b == 0 ? p_si : mc.p_ir, ds, b == 0 ? NAN : mc.l1p_ir,
+                                              mc.f1_ir);
             nsi = b == 0 ? v : nsi;
             nir = b == 1 ? v : nir;
         }
@@ -320,7 +324,7 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
             const int32_t n = b == 0 ? S : (b == 1 ? E : I);
             const real p = b == 0 ? p_se : (b == 1 ? mc.p_ei : mc.p_ir);
             const double l1p = b == 0 ? NAN : (b == 1 ? mc.l1p_ei : mc.l1p_ir);
-            const int32_t v = binomial<real>(n, p, ds, l1p);
+            const int32_t v = binomial<real>(n, p, ds, l1p, b == 1 ? mc.f1_ei : mc.f1_ir);
             nse = b == 0 ? v : nse;
             nei = b == 1 ? v : nei;
             nir = b == 2 ? v : nir;
@@ -370,7 +374,7 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
                 const int32_t n = b == 0 ? S : (b == 1 ? E : I);
                 const real p = b == 0 ? p_se : (b == 1 ? mc.p_ei : mc.p_ir);
                 const double l1p = b == 0 ? NAN : (b == 1 ? mc.l1p_ei : mc.l1p_ir);
-                const int32_t v = binomial<real>(n, p, ds, l1p);
+                const int32_t v = binomial<real>(n, p, ds, l1p, b == 1 ? mc.f1_ei : mc.f1_ir);
                 nse = b == 0 ? v : nse;
                 nei = b == 1 ? v : nei;
                 nir = b == 2 ? v : nir;
@@ -469,7 +473,7 @@ __device__ __forceinline__ bool item_begin(const MConst<real>& mc, const int32_t
     flip = p > (real)0.5;
     pp = flip ? (real)1 - p : p;
     if ((real)n * pp < (real)10) {
-        const int32_t k = binom_inversion<real>(n, pp, l1p, ds.call(0u).x);
+        const int32_t k = binom_inversion<real>(n, pp, l1p, b == ND - 1 ? mc.f1_ir : mc.f1_ei, ds.call(0u).x);
         res = flip ? n - k : k;
         return true;
     }
