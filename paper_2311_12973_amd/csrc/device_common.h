@@ -510,6 +510,27 @@ __device__ __forceinline__ int32_t binom_btrs(int32_t n, real p, const DrawStrea
     return btrs_mode<real>(n, p);
 }
 
+// A draw's attempts 0 and 1, one Philox call, as far as one final test goes: attempt 0's when
+// attempt 0 needs it, attempt 1's when attempt 0 lies outside [0, n]. True when that settles
+// the draw (k is set, the same value as binom_btrs gives): the test runs once for the whole
+// wave instead of once an attempt, and one draw in fourteen stays open (from attempt 1 on).
+template <typename real>
+__device__ __forceinline__ bool btrs_first(int32_t n, real p, const DrawStream& s, int32_t& k)
+{
+    const BtrsConst<real> c = btrs_setup<real>(n, p);
+    const W4 w = s.call(0u);
+    int32_t k0 = 0, k1 = 0;
+    const int t0 = btrs_try<real>(c, n, w.x, w.y, k0), t1 = btrs_try<real>(c, n, w.z, w.w, k1);
+    const bool out = t0 == BTRS_OUT;
+    const int t = out ? t1 : t0;
+    k = out ? k1 : k0;
+    bool acc = t == BTRS_ACCEPT;
+    if (t == BTRS_FINAL) acc = btrs_decide<real>(c, n, p, k, out ? w.z : w.x, out ? w.w : w.y);
+    const bool second = !acc & !out & (t1 == BTRS_ACCEPT);
+    k = second ? k1 : k;
+    return acc | second;
+}
+
 // Binomial(n, p). l1p, when not NaN, is log1p(-min(p, 1-p)) precomputed in FP64, and f1
 // its exponential rounded to `real`.
 template <typename real>
@@ -524,6 +545,25 @@ __device__ __forceinline__ int32_t binomial(int32_t n, real p, const DrawStream&
         k = binom_inversion<real>(n, pp, l1p, f1, s.call(0u).x);
     } else {
         k = binom_btrs<real>(n, pp, s);
+    }
+    return flip ? n - k : k;
+}
+
+// The same value, or 0 with open set when its first attempts (btrs_first) leave it open.
+template <typename real>
+__device__ __forceinline__ int32_t binomial_first(int32_t n, real p, const DrawStream& s, double l1p, real f1, bool& open)
+{
+    open = false;
+    if (n <= 0 || !(p > (real)0)) return 0;
+    if (p >= (real)1) return n;
+    const bool flip = p > (real)0.5;
+    const real pp = flip ? (real)1 - p : p;
+    int32_t k = 0;
+    if ((real)n * pp < (real)10) {
+        k = binom_inversion<real>(n, pp, l1p, f1, s.call(0u).x);
+    } else if (!btrs_first<real>(n, pp, s, k)) {
+        open = true;
+        return 0;
     }
     return flip ? n - k : k;
 }

@@ -108,3 +108,21 @@ def test_few_filters_take_wider_workgroups_with_the_same_results(preset, nx, n):
     a = G.pf_loglik(w, theta, y, nx, seed=3, k=1)
     b = G.pf_loglik(w, theta, y, nx, seed=3, k=1, block=128)
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("nx", [1, 63, 64, 65, 200])
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+@pytest.mark.parametrize("preset", ["sir_fp64", "seir", "age_seir"])
+def test_per_draw_filters_settle_their_open_draws(preset, prec, nx):
+    """Flows of about n p = 10 to 20, where the rejection sampler accepts least: most waves are
+    left with open draws after the first pass, the age-structured ones with more than 64 at
+    once, and in whole, partly filled and nearly empty waves alike."""
+    w = dict(W.preset(preset), n_pop=4000.0, T=8)
+    truth = np.array(w["truth"])
+    if preset == "sir_fp64":
+        w["fixed"], truth[1] = [120], 0.12
+    else:
+        truth[1:4] = 0.12, 0.15, 0.1 if preset == "age_seir" else 0.025
+    y = np.full((8, 4 if preset == "age_seir" else 1), 12, dtype=np.int32)
+    theta = np.tile(truth, (6, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (6, w["D"])))
+    _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW)
