@@ -126,3 +126,18 @@ def test_per_draw_filters_settle_their_open_draws(preset, prec, nx):
     y = np.full((8, 4 if preset == "age_seir" else 1), 12, dtype=np.int32)
     theta = np.tile(truth, (6, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (6, w["D"])))
     _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW)
+
+
+@pytest.mark.parametrize("nx", [1, 64, 65, 130])
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+@pytest.mark.parametrize("late", [0, 1])
+def test_age_structured_epidemics_that_burn_out(late, prec, nx):
+    """Particles without anyone exposed or infected: whole waves of them and waves with a few
+    left, on days that report no case, and on a last day that reports one (weight zero)."""
+    w = dict(W.preset("age_seir"), n_pop=400.0, T=40)
+    truth = np.array(w["truth"])
+    truth[:4] = 0.4, 0.5, 0.6, 0.01
+    y = np.zeros((40, 4), dtype=np.int32)
+    y[3:8, 1], y[-1, 2] = 1, late
+    theta = np.tile(truth, (6, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.2, (6, w["D"])))
+    _same_filters(w, theta, y, nx, prec=prec)
