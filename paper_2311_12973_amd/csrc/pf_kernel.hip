@@ -982,7 +982,11 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             constexpr int G = DrawGroups<MODEL>::G;
             const int ptotal = (SCORE || a.prio_scale > 0.f) ? 0 : (cap / nthr) * G;
             // whole waves, so that a wave settles its open draws with all lanes
-            for (int j = tid, pass = 0; uniform_i32(j) < nx; j += nthr, ++pass) {
+            // a wave without particles in the last pass starts one pass further on, so that those
+            // with more to do outrank it (4096 filters, N_x = 300 on 256 threads: SEIR, 100 days,
+            // 7.37 -> 6.90 ms; FP64 SIR, 50 days, 3.80 -> 3.35 ms)
+            const int ahead = cap - nthr + uniform_i32(tid) < nx ? 0 : 1;
+            for (int j = tid, pass = ahead; uniform_i32(j) < nx; j += nthr, ++pass) {
                 const bool live = j < nx;
                 const real lg = particle_day<real, MODEL, OBS, SCORE>(
                     mc, st, flows, cap, j, live, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1}, yt, sd,
