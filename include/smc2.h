@@ -117,9 +117,10 @@ extern "C" {
                                (Eq. l_weights). Iteration 1 draws from the prior. */
 
 /* particle-filter draw schedule (smc2_config.schedule); both give identical results */
-#define SMC2_SCHED_AUTO 0     /* pooled where supported and it fits in LDS, else per draw
+#define SMC2_SCHED_AUTO 0     /* per draw, except SIR/SEIR shapes where pooled is faster
                                  (the score launches of SMC2_PROP_LANGEVIN: per draw)     */
-#define SMC2_SCHED_PER_DRAW 1 /* each lane finishes its draws one after another          */
+#define SMC2_SCHED_PER_DRAW 1 /* each lane takes its draws one after another; a wave
+                                 settles those that its first attempts left open         */
 #define SMC2_SCHED_POOLED 2   /* SIR/SEIR: a wave pools its draws and runs the final
                                  acceptance tests of the BTRS sampler 64 at a time        */
 

@@ -48,9 +48,10 @@ struct PFArgs {
     double fx[32];          // model constants
 };
 
-// How a workgroup schedules the binomial draws of a day: every lane finishes its own
-// draws in turn, or (SIR, SEIR) the wave pools the draws and batches the final
-// acceptance tests of the BTRS sampler. Both give identical flows.
+// How a workgroup schedules the binomial draws of a day: every lane takes its particle's
+// draws in turn and the wave then settles those still open, or (SIR, SEIR) the waves pool
+// the draws and batch the final acceptance tests of the BTRS sampler. Both give identical
+// flows.
 enum : int { PF_SCHED_AUTO = 0, PF_SCHED_PER_DRAW = 1, PF_SCHED_POOLED = 2 };
 // Internal launch variants that also carry each particle's running score of its
 // trajectory and write the filter's score estimate: on the per-draw schedule (SIR, SEIR
@@ -67,8 +68,8 @@ constexpr size_t PF_LDS_MAX = 160 * 1024 - 256;
 
 // Dynamic LDS bytes of one filter workgroup.
 size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched);
-// The kernel variant to run for a requested draw schedule (PF_SCHED_AUTO: pooled where
-// supported and it fits in LDS), with score = true its score-carrying form; -1 when
+// The kernel variant to run for a requested draw schedule (PF_SCHED_AUTO: per draw, except
+// where the pooled one measured faster), with score = true its score-carrying form; -1 when
 // the pooled schedule was requested but cannot run, or the model has no score.
 int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requested, bool score = false);
 // Default workgroup size for a filter of this shape (64 .. 1024 threads), in a launch of

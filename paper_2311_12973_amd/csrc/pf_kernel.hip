@@ -1204,25 +1204,69 @@ static int pf_few_filters_block(int model, int prec, int nx, int T, int requeste
     const int per_cu = n_filters <= 256 ? 1 : 2;
     const int full = ((nx + 63) / 64) * 64;
     const int most = full < 1024 / per_cu ? full : 1024 / per_cu;
-    // the widest that runs pooled, down to half of the most; else the most on the per-draw schedule
-    int widest = 0;
     for (int b = most; 2 * b >= most && b >= 64; b -= 64) {
         const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
-        if (sc < 0 || pf_lds_bytes(model, prec, b, nx, T, sc) * per_cu > PF_LDS_MAX) continue;
-        if (widest == 0) widest = b;
-        if (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED) return b;
+        if (sc >= 0 && pf_lds_bytes(model, prec, b, nx, T, sc) * per_cu <= PF_LDS_MAX) return b;
     }
-    return widest;
+    return 0;
+}
+
+// Larger launches: the workgroup size of the least estimated time, in units of a pass over a
+// workgroup's particles with all 16 wave slots of a CU taken. What enters, each fitted to one
+// series of measurements (SEIR, per draw) and then right, or within 2%, at 45 of 48 others (SEIR
+// with and without scores, FP64 SIR, linear-Gaussian and age-structured, 700 to 12288 filters,
+// N_x = 100 to 2000; the other three within 9%):
+//  - a pass with W resident waves takes 0.46 + 0.54 W / 16 (1000 filters, N_x = 512: 4, 8, 16
+//    waves a CU take 8, 4, 2 passes in 5.04, 3.09, 2.12 ms): narrow workgroups serve the launch
+//    whose filters are all resident, wide ones the one of few filters;
+//  - a wave with a pass more than the average holds up its workgroup for 0.6 of the difference
+//    (the other workgroups of the CU fill in the rest);
+//  - filters beyond those resident at once (by LDS and wave slots) wait for the next round, and
+//    the workgroups of several rounds fall out of step: 15% more, 3% for a single wave, which
+//    never waits at a barrier.
+// Against the size before (the most waves resident, at least 256 threads): 2048 filters, N_x =
+// 512, 60 days 2.93 -> 2.52 ms; 4096, N_x = 128, 1.87 -> 1.36 ms; 3000, N_x = 257, 3.10 -> 2.41.
+static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
+{
+    static const int sizes[] = {64, 128, 192, 256, 512, 1024};
+    const int full = ((nx + 63) / 64) * 64;
+    const auto pass_time = [](double waves) { return 0.46 + 0.54 * waves / 16.0; };
+    int best = 0;
+    double best_time = 0.0;
+    for (int b : sizes) {
+        if (b > full) break;
+        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
+        if (sc < 0) continue;
+        const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
+        if (lds > PF_LDS_MAX) continue;
+        const int w = b / 64, by_lds = (int)(PF_LDS_MAX / lds), per_cu = by_lds < 16 / w ? by_lds : 16 / w;
+        const int rounds = n_filters / (256 * per_cu), last = (n_filters - rounds * 256 * per_cu + 255) / 256;
+        double time = rounds * pass_time(per_cu * w) + (last > 0 ? pass_time(last * w) : 0.0);
+        const bool several = n_filters > 256 * per_cu;
+        if (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED) {
+            time *= (0.75 + 0.68 * nx / b) * (several ? 1.05 : 1.0);  // its waves share the passes
+        } else {
+            const double mean = (double)(full / 64) / w, most = (double)((nx + b - 1) / b);
+            time *= (mean + 0.6 * (most - mean)) * (several ? (w == 1 ? 1.03 : 1.15) : 1.0);
+        }
+        if (best == 0 || time < best_time) {
+            best = b;
+            best_time = time;
+        }
+    }
+    return best;
 }
 
 int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
 {
-    if (n_filters > 0 && n_filters <= 512) {
-        const int b = pf_few_filters_block(model, prec, nx, T, requested_sched, score, n_filters);
+    if (n_filters > 0) {
+        const int b = n_filters <= 512
+                          ? pf_few_filters_block(model, prec, nx, T, requested_sched, score, n_filters)
+                          : pf_many_filters_block(model, prec, nx, T, requested_sched, score, n_filters);
         if (b > 0) return b;
     }
-    // the workgroup size that keeps the most waves resident per CU (LDS allowing,
-    // at most 16 at 128 VGPRs), preferring the pooled schedule by its measured gain
+    // launches of runs of different sizes: the workgroup size that keeps the most waves resident
+    // per CU (LDS allowing, at most 16 at 128 VGPRs), preferring the pooled schedule where it is taken
     const int full = ((nx + 63) / 64) * 64;
     int best = full < 256 ? full : 256;
     double best_score = -1.0;
@@ -1261,7 +1305,12 @@ int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requeste
                            pf_lds_bytes(model, prec, block, nx, T, PF_SCHED_POOLED) <= PF_LDS_MAX;
     if (requested == PF_SCHED_PER_DRAW) return PF_SCHED_PER_DRAW;
     if (requested == PF_SCHED_POOLED) return pooled_ok ? PF_SCHED_POOLED : -1;
-    return pooled_ok ? PF_SCHED_POOLED : PF_SCHED_PER_DRAW;
+    // automatic: per draw, but for two passes of 256 threads with the second partly filled, which
+    // the pooled schedule spreads over all waves (SEIR, 100 days, pooled against per draw: 700
+    // filters, N_x = 300, 1.50 against 1.64 ms; 1000, N_x = 333, 1.81 against 1.90; N_x = 257, 1.66
+    // against 1.56; N_x = 512, 2.15 against 2.12; N_x = 1000, 4.45 against 3.86)
+    const bool ragged = block == 256 && nx >= 288 && nx < 448;
+    return pooled_ok && ragged ? PF_SCHED_POOLED : PF_SCHED_PER_DRAW;
 }
 
 template <typename real, int MODEL, int OBS, int SCHED>
