@@ -275,6 +275,28 @@ template <typename real> __device__ __forceinline__ real lane_push(real v, int t
     }
 }
 
+// A particle's probability of leaving S, kept for the day's open draws and score beside the flows:
+// in the fourth row of flows in FP32, in the third and fourth for SIR in FP64. SEIR's three rows of
+// flows leave an FP64 value no room: there it is computed again from the day-start counts.
+template <typename real, int MODEL> struct KeptProb {
+    static constexpr bool KEPT = sizeof(real) == 4 || MODEL == MODEL_SIR;
+    static __device__ __forceinline__ void put(int32_t* flows, int cap, int j, real p)
+    {
+        if constexpr (sizeof(real) == 4) {
+            flows[3 * cap + j] = __float_as_int(p);
+        } else if constexpr (KEPT) {
+            flows[2 * cap + j] = __double2loint(p);
+            flows[3 * cap + j] = __double2hiint(p);
+        }
+    }
+    static __device__ __forceinline__ real get(const MConst<real>& mc, const int32_t* st, const int32_t* flows, int cap, int j)
+    {
+        if constexpr (sizeof(real) == 4) return __int_as_float(flows[3 * cap + j]);
+        else if constexpr (KEPT) return lds_f64(flows + 2 * cap, cap, j);
+        else return leave_prob<real>(mc.cinf * (real)st[(ModelShape<MODEL>::NC - 1) * cap + j]);
+    }
+};
+
 // The per-draw schedule draws in two steps. First every lane takes its particle's draws in
 // order, each as far as attempts 0 and 1 and one final test go (binomial_first); a draw that
 // stays open, one rejection draw in fourteen, sets its bit in the lane's mask. Then the wave
@@ -291,29 +313,35 @@ template <typename real> __device__ __forceinline__ real lane_push(real v, int t
 // (256 rejected attempts give the mode). Every attempt is a function of its Philox coordinates
 // alone, so the flows do not depend on the lane that draws them.
 //
-// All lanes active; j0 is the particle of lane 0, ps the groups' leave probabilities of S.
-// SIR and SEIR: flows[d * cap + j] holds draw d's flow and st the day-start counts; the flow of
-// an open draw is set here. Age-structured (draw d leaves compartment d): st already holds the
-// counts with the settled flows applied and flows[g * cap + j] the flow out of E, or, while that
+// All lanes active; j0 is the particle of lane 0. Bit d = PER gr + b of a lane's mask stands for
+// the flow out of compartment b of its group gr, gr < n_groups:
+// SIR and SEIR: gr counts passes of blockDim particles; the draws of all passes are settled at
+// once (13 open draws a wave and pass fill a batch only over several: 1000 SEIR filters, N_x =
+// 1000, 150 days, against a batch a pass 5.90 -> 5.29 ms; learned sampler, 4096 filters x 1024 x
+// 150, 79.9 -> 71.3 ms; one pass, with scores, 1.57 -> 1.61). flows[b * cap + j] holds the flows
+// and st the day-start counts; the flow of an open draw is set here.
+// Age-structured: gr is the age group, ps its leave probabilities of S. st already holds the
+// counts with the settled flows applied and flows[gr * cap + j] the flow out of E, or, while that
 // draw is open, the day-start E. An open S still holds its day-start count; an open I has gained
 // the flow out of E unless that one is open too, which it then still is (descending order).
-template <typename real, int MODEL, int NP>
+template <typename real, int MODEL>
 __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st, int32_t* flows, int cap, int j0,
-                                            uint32_t open, const real (&ps)[NP], DrawStream ds)
+                                            uint32_t open, int n_groups, const real (&ps)[4], DrawStream ds)
 {
-    constexpr int ND = ModelShape<MODEL>::NC, PER = MODEL == MODEL_SIR ? 2 : 3;
+    constexpr bool AGE = MODEL == MODEL_AGE;
+    constexpr int PER = MODEL == MODEL_SIR ? 2 : 3;
     const int lane = lane_id();
     const uint64_t below = lanes_below();
     const uint32_t before = open << 1;  // bit d: draw d - 1 is open
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     while (__ballot(open != 0u) != 0ull) {
-        // deal: slot s of the batch gets 1 + (owner's lane | d << 6 | (draw d - 1 open) << 10).
+        // deal: slot s of the batch gets 1 + (owner's lane | d << 6 | (draw d - 1 open) << 11).
         // All of a draw index or none, so the first one always fits.
         uint32_t item = 0;
         real ip = (real)0;
         int cnt = 0;
 #pragma nounroll
-        for (int d = ND - 1, b = PER - 1, gr = NP - 1; d >= 0; --d) {
+        for (int d = PER * n_groups - 1, b = PER - 1, gr = n_groups - 1; d >= 0; --d) {
             const bool mine = ((open >> d) & 1u) != 0u;
             const uint64_t m = __ballot(mine);
             const int c = __popcll(m);
@@ -321,14 +349,11 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
             if (c > 0) {
                 const int rank = __popcll(m & below);
                 const int to = (mine ? cnt + rank : cnt + c + lane - rank) & 63;
-                const uint32_t id = 1u + (uint32_t)(lane | (d << 6) | (int)(((before >> d) & 1u) << 10));
+                const uint32_t id = 1u + (uint32_t)(lane | (d << 6) | (int)(((before >> d) & 1u) << 11));
                 const uint32_t got = (uint32_t)__builtin_amdgcn_ds_permute(to << 2, (int)(mine ? id : 0u));
                 item = got ? got : item;
-                if (b == 0) {
-                    real p = ps[0];
-#pragma unroll
-                    for (int h = 1; h < NP; ++h) p = gr == h ? ps[h] : p;
-                    const real pg = lane_push<real>(p, to);
+                if (AGE && b == 0) {
+                    const real pg = lane_push<real>(gr == 0 ? ps[0] : (gr == 1 ? ps[1] : (gr == 2 ? ps[2] : ps[3])), to);
                     ip = got ? pg : ip;
                 }
                 open &= ~(1u << d);
@@ -340,23 +365,27 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
         const int lr = cnt > 32 ? 0 : (cnt > 16 ? 1 : (cnt > 8 ? 2 : (cnt > 4 ? 3 : (cnt > 2 ? 4 : (cnt > 1 ? 5 : 6)))));
         const int r = 1 << lr, slot = lane >> lr, jj = lane & (r - 1);
         const uint32_t id = (uint32_t)__shfl((int)item, slot) - 1u;
-        real p = __shfl(ip, slot);
+        real p = AGE ? __shfl(ip, slot) : (real)0;
         bool todo = slot < cnt;
-        int32_t n = 0, d = 0, jo = 0, b = 0, gr = 0;
+        int32_t n = 0, jo = 0, b = 0, gr = 0;
+        int32_t* from = st;  // the count that the flow leaves
         bool flip = false;
         BtrsConst<real> c{};
         BtrsFinal fs{};
         if (todo) {
-            d = (int)((id >> 6) & 15u);
-            jo = j0 + (int)(id & 63u);
+            const int d = (int)((id >> 6) & 31u);
+            gr = PER == 2 ? d >> 1 : (d * 11) >> 5;  // d / 3
+            b = d - PER * gr;
+            jo = j0 + (int)(id & 63u) + (AGE ? 0 : gr * (int)blockDim.x);
             ds.j = (uint32_t)jo;
-            ds.b = (uint32_t)d;
-            gr = MODEL == MODEL_AGE ? (d * 11) >> 5 : 0;  // d / 3
-            b = d - 3 * gr;
-            n = st[d * cap + jo];
-            if constexpr (MODEL == MODEL_AGE) {
+            ds.b = (uint32_t)(AGE ? d : b);
+            from = st + (AGE ? d : b) * cap + jo;
+            n = *from;
+            if constexpr (AGE) {
                 const int32_t f = flows[gr * cap + jo];
-                n = b == 1 ? f : (b == 2 && !((id >> 10) & 1u) ? n - f : n);
+                n = b == 1 ? f : (b == 2 && !((id >> 11) & 1u) ? n - f : n);
+            } else {
+                p = KeptProb<real, MODEL>::get(mc, st, flows, cap, jo);
             }
             p = b == 0 ? p : (b == PER - 1 ? mc.p_ir : mc.p_ei);
             flip = p > (real)0.5;
@@ -389,12 +418,12 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
             if (todo && gm) {
                 if ((slot << lr) + (int)__builtin_ctzll(gm) == lane) {
                     const int32_t v = flip ? n - k : k;
-                    if constexpr (MODEL == MODEL_AGE) {
-                        lds_add_i32(&st[d * cap + jo], -v);
-                        if (b < 2) lds_add_i32(&st[(d + 1) * cap + jo], v);
+                    if constexpr (AGE) {
+                        lds_add_i32(from, -v);
+                        if (b < 2) lds_add_i32(from + cap, v);
                         if (b == 1) flows[gr * cap + jo] = v;
                     } else {
-                        flows[d * cap + jo] = v;
+                        flows[b * cap + jo] = v;
                     }
                 }
                 todo = false;
@@ -442,19 +471,41 @@ __device__ __forceinline__ real particle_update(const MConst<real>& mc, int32_t*
     }
 }
 
-// One day of the chain-binomial model for particle j, whose counts live in LDS
-// (st[c * cap + j]); flows drawn from the previous day's state. Draw index b:
-// SIR (S->I, I->R) = (0, 1); SEIR (S->E, E->I, I->R) = (0, 1, 2); age-structured
-// group g: 3g, 3g+1, 3g+2 (the draw index equals the index of the compartment the
-// flow leaves). One copy of the sampler per model: the draws of a day run in a
-// loop. All lanes active, with live unset those beyond the particles. Returns the per-particle
-// part of log g(y_t | x_t), its FP64 value rounded to `real`. With SCORE it adds
-// the day's complete-data score to the particle's: per flow d log Bin / d h times
-// d h / d theta (I / N_pop for beta, 1 for sigma and gamma), d log g / d r, and for the
-// linear-Gaussian model the derivatives of its two Gaussian densities. With ptotal > 0
-// each draw group first sets the wave's issue priority (progress_priority, step pbase +
-// group of ptotal).
-template <typename real, int MODEL, int OBS, bool SCORE = false>
+// The day's draws of particle j, whose counts live in LDS (st[c * cap + j]), under SIR or SEIR, as
+// far as binomial_first takes them, from the day-start counts: flows to flows[b * cap + j], the
+// open ones as a mask. Draw index b: SIR (S->I, I->R) = (0, 1); SEIR (S->E, E->I, I->R) =
+// (0, 1, 2), in a loop: one copy of the sampler. With ptotal > 0 each draw first sets the wave's
+// issue priority (progress_priority, step pbase + b of ptotal).
+template <typename real, int MODEL>
+__device__ __forceinline__ uint32_t particle_draws(const MConst<real>& mc, const int32_t* st, int32_t* flows, int cap,
+                                                   int j, DrawStream ds, int pbase, int ptotal)
+{
+    constexpr int ND = ModelShape<MODEL>::NC;
+    const real p_s = leave_prob<real>(mc.cinf * (real)st[(ND - 1) * cap + j]);
+    KeptProb<real, MODEL>::put(flows, cap, j, p_s);
+    uint32_t open = 0;
+#pragma nounroll
+    for (int b = 0; b < ND; ++b) {
+        if (ptotal > 0) progress_priority(pbase + b, ptotal);
+        ds.b = (uint32_t)b;
+        const int32_t n = st[b * cap + j];
+        const real p = b == 0 ? p_s : (b == ND - 1 ? mc.p_ir : mc.p_ei);
+        const double l1p = b == 0 ? NAN : (b == ND - 1 ? mc.l1p_ir : mc.l1p_ei);
+        bool left;
+        flows[b * cap + j] = binomial_first<real>(n, p, ds, l1p, b == ND - 1 ? mc.f1_ir : mc.f1_ei, left);
+        open |= (uint32_t)left << b;
+    }
+    return open;
+}
+
+// One day of the linear-Gaussian or the age-structured model for particle j, whose state lives in
+// LDS (st[c * cap + j]); flows drawn from the previous day's state, age group g's with draw
+// index b = 3g, 3g+1, 3g+2 (the compartment that the flow leaves) in a loop: one copy of the
+// sampler. All lanes active, with live unset those beyond the particles. Returns the per-particle
+// part of log g(y_t | x_t), its FP64 value rounded to `real`. With SCORE (linear-Gaussian) it adds
+// the derivatives of the two Gaussian densities to the particle's score. With ptotal > 0 each draw
+// group first sets the wave's issue priority (progress_priority, step pbase + group of ptotal).
+template <typename real, int MODEL, bool SCORE = false>
 __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st, int32_t* flows, int cap, int j,
                                              bool live, DrawStream ds, const int32_t* yt, const ScoreDay& sd = ScoreDay{},
                                              int pbase = 0, int ptotal = 0)
@@ -477,25 +528,7 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
         }
         return (real)(-0.5 * z * z);
     }
-    if constexpr (MODEL == MODEL_SIR || MODEL == MODEL_SEIR) {
-        constexpr int ND = ModelShape<MODEL>::NC;
-        const real ps[1] = {leave_prob<real>(mc.cinf * (real)st[(ND - 1) * cap + j])};
-        uint32_t open = 0;
-#pragma nounroll
-        for (int b = 0; b < ND; ++b) {
-            if (ptotal > 0) progress_priority(pbase + b, ptotal);
-            ds.b = (uint32_t)b;
-            const int32_t n = st[b * cap + j];
-            const real p = b == 0 ? ps[0] : (b == ND - 1 ? mc.p_ir : mc.p_ei);
-            const double l1p = b == 0 ? NAN : (b == ND - 1 ? mc.l1p_ir : mc.l1p_ei);
-            bool left;
-            flows[b * cap + j] = binomial_first<real>(n, p, ds, l1p, b == ND - 1 ? mc.f1_ir : mc.f1_ei, left);
-            open |= (uint32_t)left << b;
-        }
-        settle_open<real, MODEL, 1>(mc, st, flows, cap, j - lane_id(), open, ps, ds);
-        if (!live) return (real)0;
-        return particle_update<real, MODEL, OBS, SCORE>(mc, st, flows, cap, j, ps[0], yt, sd);
-    } else {
+    if constexpr (MODEL == MODEL_AGE) {
         // Without anyone exposed or infected in the wave's particles nothing moves any more: no
         // flow, and every series expects no case. An epidemic that has burnt out spends the rest
         // of its days here, a third of a wave's 365 near the posterior (2048 filters x 2048 x 365,
@@ -544,7 +577,7 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
             st[(3 * g + 2) * cap + j] = I + nei - nir;
             flows[g * cap + j] = (open >> (3 * g + 1)) & 1u ? E : nei;
         }
-        settle_open<real, MODEL, 4>(mc, st, flows, cap, j - lane_id(), open, ps, ds);
+        settle_open<real, MODEL>(mc, st, flows, cap, j - lane_id(), open, 4, ps, ds);
         // the observation terms after the draws, four independent chains at once; the
         // day's new cases wait in the weight and gather buffers, free while drawing
         int32_t mu[4];
@@ -963,32 +996,49 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
         real amax = (real)-INFINITY;
         ScoreDay sd{};
         if constexpr (SCORE) sd = ScoreDay{sw, a.n_pop, DPSI ? dps[t - 1] : 0.0, MODEL == MODEL_SEIR && a.D >= 5};
-        if constexpr (POOLED) {
-            draws_pooled<real, MODEL>(mc, st, flows, cap, nx, pool, filt, kt, run.k0, run.k1, &wg_next);
-            __syncthreads();  // any wave may have drawn any particle's flows
-            if (tid == 0) wg_next = 0;  // for the next day (read again only after further barriers)
+        // without the filter-level priority, each wave's from its progress through the day's draws;
+        // not in score launches, whose two filters per CU ran 4% slower with it over 4096
+        // filters (1% faster over 40960; the plain per-draw launch at four filters per CU
+        // ran 3-5% faster, one per CU 6-7%). A wave without particles in the last pass starts one
+        // pass further on, so that those with more to do outrank it (4096 filters, N_x = 300 on 256
+        // threads: SEIR, 100 days, 7.37 -> 6.90 ms; FP64 SIR, 50 days, 3.80 -> 3.35 ms)
+        constexpr int G = DrawGroups<MODEL>::G;
+        const int ptotal = (SCORE || a.prio_scale > 0.f) ? 0 : (cap / nthr) * G;
+        int pass = cap - nthr + uniform_i32(tid) < nx ? 0 : 1;
+        if constexpr (MODEL == MODEL_SIR || MODEL == MODEL_SEIR) {
+            if constexpr (POOLED) {
+                draws_pooled<real, MODEL>(mc, st, flows, cap, nx, pool, filt, kt, run.k0, run.k1, &wg_next);
+                __syncthreads();  // any wave may have drawn any particle's flows
+                if (tid == 0) wg_next = 0;  // for the next day (read again only after further barriers)
+            } else {
+                // whole waves, each its own particles, as many passes as a mask of open draws holds
+                for (int j = tid; uniform_i32(j) < nx;) {
+                    const int j0 = j - lane_id();
+                    uint32_t open = 0;
+                    int np = 0;
+                    for (; np < 32 / NC && uniform_i32(j) < nx; ++np, ++pass, j += nthr)
+                        open |= particle_draws<real, MODEL>(
+                                    mc, st, flows, cap, j, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1},
+                                    pass * G, ptotal)
+                                << (NC * np);
+                    const real none[4] = {};
+                    settle_open<real, MODEL>(mc, st, flows, cap, j0, open, np, none,
+                                             DrawStream{0u, filt, kt, 0u, run.k0, run.k1});
+                }
+            }
             for (int j = tid; j < nx; j += nthr) {
                 real p_s = (real)0;
-                if constexpr (SCORE) p_s = leave_prob<real>(mc.cinf * (real)st[(NC - 1) * cap + j]);
+                if constexpr (SCORE && POOLED) p_s = leave_prob<real>(mc.cinf * (real)st[(NC - 1) * cap + j]);
+                else if constexpr (SCORE) p_s = KeptProb<real, MODEL>::get(mc, st, flows, cap, j);
                 const real av = lw[j] + particle_update<real, MODEL, OBS, SCORE>(mc, st, flows, cap, j, p_s, yt, sd);
                 lw[j] = av;
                 amax = av > amax ? av : amax;
             }
         } else {
-            // without the filter-level priority, each wave's from its progress through the day;
-            // not in score launches, whose two filters per CU ran 4% slower with it over 4096
-            // filters (1% faster over 40960; the plain per-draw launch at four filters per CU
-            // ran 3-5% faster, one per CU 6-7%)
-            constexpr int G = DrawGroups<MODEL>::G;
-            const int ptotal = (SCORE || a.prio_scale > 0.f) ? 0 : (cap / nthr) * G;
             // whole waves, so that a wave settles its open draws with all lanes
-            // a wave without particles in the last pass starts one pass further on, so that those
-            // with more to do outrank it (4096 filters, N_x = 300 on 256 threads: SEIR, 100 days,
-            // 7.37 -> 6.90 ms; FP64 SIR, 50 days, 3.80 -> 3.35 ms)
-            const int ahead = cap - nthr + uniform_i32(tid) < nx ? 0 : 1;
-            for (int j = tid, pass = ahead; uniform_i32(j) < nx; j += nthr, ++pass) {
+            for (int j = tid; uniform_i32(j) < nx; j += nthr, ++pass) {
                 const bool live = j < nx;
-                const real lg = particle_day<real, MODEL, OBS, SCORE>(
+                const real lg = particle_day<real, MODEL, SCORE>(
                     mc, st, flows, cap, j, live, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1}, yt, sd,
                     pass * G, ptotal);
                 if (live) {

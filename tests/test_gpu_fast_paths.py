@@ -141,3 +141,19 @@ def test_age_structured_epidemics_that_burn_out(late, prec, nx):
     y[3:8, 1], y[-1, 2] = 1, late
     theta = np.tile(truth, (6, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.2, (6, w["D"])))
     _same_filters(w, theta, y, nx, prec=prec)
+
+
+@pytest.mark.parametrize("preset,nx", [("sir_fp64", 1024), ("sir_fp64", 1025), ("seir", 640), ("seir", 641)])
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+def test_open_draws_of_many_passes(preset, nx, prec):
+    """One wave with as many passes as its mask of open draws holds (SIR 16, SEIR 10) and one
+    particle more, several batches of open draws a day."""
+    w = dict(W.preset(preset), n_pop=4000.0, T=5)
+    truth = np.array(w["truth"])
+    if preset == "sir_fp64":
+        w["fixed"], truth[1] = [120], 0.12
+    else:
+        truth[1:4] = 0.12, 0.15, 0.025
+    y = np.full((5, 1), 12, dtype=np.int32)
+    theta = np.tile(truth, (3, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (3, w["D"])))
+    _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW, block=64)
