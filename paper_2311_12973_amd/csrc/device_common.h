@@ -360,11 +360,14 @@ __device__ __forceinline__ bool btrs_final(const BtrsConst<real>& c, int32_t n, 
 // the FP64 decision. Needs n < 2^23 (integers exact in FP32). For the FP64 filters the set-up
 // values and p enter rounded to FP32, one more unit each.
 // The test is bound by instruction issue, and a wave runs it whenever one lane needs it: 2.5
-// times a draw on the per-draw schedule, with 15% of its lanes. What depends on (n, p) alone
-// is therefore computed once a draw (BtrsFinal, 48 vector instructions), leaving about 80 a
-// test, against 735 for the FP64 test (FP64 SIR sampler, 1024 filters x 500 x 30, ten
-// iterations: 10.3 -> 7.8 ms; the age-structured sampler, 140 a test -> this: 287 -> 257 ms,
-// Langevin 12.1 -> 11.4 ms).
+// times a draw when each attempt runs in place. What depends on (n, p) alone is therefore computed
+// once a draw (BtrsFinal, 50 vector instructions), leaving about 90 a test, against 735 for the
+// FP64 test (FP64 SIR sampler, 1024 filters x 500 x 30, ten iterations: 10.3 -> 7.8 ms; the
+// age-structured sampler, 140 a test -> this: 287 -> 257 ms, Langevin 12.1 -> 11.4 ms).
+// Reciprocals and logarithms issue at a quarter of the rate: products share one reciprocal and the
+// two logarithms that always enter are one, five of them a test for eight and two a set-up for
+// four (1000 SEIR filters, N_x = 1000, 150 days: 5.29 -> 5.16 ms; 50 age-structured filters,
+// N_x = 1500, 200 days: 10.2 -> 9.9 ms).
 static __constant__ float c_fc_tab[4] = {0.081061466795327f, 0.041340695955409f, 0.027677925684998f,
                                         0.020790672103766f};
 
@@ -415,14 +418,17 @@ template <typename real> __device__ __forceinline__ BtrsFinal btrs_final_setup(c
     s.m = (int32_t)mp;
     const float fr = (float)__builtin_amdgcn_fract(mp);
     const float M = (float)(s.m + 1), N = (float)(n - s.m + 1);
-    s.rM = fast_rcp(M);
-    s.rN = fast_rcp(N);
     const float pf = (float)p, qf = (float)q;
+    const float qM = qf * M, qN = qf * N;
+    const float r = fast_rcp(qM * N);  // all three reciprocals from one
+    s.rM = r * qN;
+    s.rN = r * qM;
     const float dq = (float)(((real)1 - q) - p);
-    const float y0 = fmaf(dq, M, (fr + pf) - 1.0f) * fast_rcp(qf * M);
+    const float y0 = fmaf(dq, M, (fr + pf) - 1.0f) * (r * N);
     s.L0 = fabsf(y0) <= 0.125f ? fmaf(y0 * y0, log1p_curve(y0), y0) : fast_ln(1.0f + y0);
     s.fmn = btrs_fc(s.rM) + btrs_fc(s.rN);
-    s.alpha = (2.83f + 5.1f * fast_rcp((float)c.bb)) * (float)c.spq;
+    // 5.1 / b from v_r = 0.92 - 4.2 / b (its rounding, 2^-25, is small beside 2.83)
+    s.alpha = fmaf(0.92f - (float)c.vr, 5.1f / 4.2f, 2.83f) * (float)c.spq;
     return s;
 }
 
@@ -438,20 +444,25 @@ __device__ __forceinline__ int btrs_final_fast(const BtrsConst<real>& c, const B
     const float A = (float)(k + 1), B = (float)(n - k + 1);
     const float u1 = df * s.rM, u2 = -df * s.rN;
     const float a1 = A * s.rM, b1 = B * s.rN;
-    const bool s1 = fabsf(u1) <= 0.125f, s2 = fabsf(u2) <= 0.125f;
-    const float h1 = s1 ? (df * u1) * entropy_curve(u1) : fmaf(A, fast_ln(a1), -df);
-    const float h2 = s2 ? (-df * u2) * entropy_curve(u2) : fmaf(B, fast_ln(b1), df);
-    const float hl = 0.5f * fast_ln(a1 * b1);
-    float fk = btrs_fc(fast_rcp(A)), fnk = btrs_fc(fast_rcp(B));
+    float h1 = (df * u1) * entropy_curve(u1), h2 = (-df * u2) * entropy_curve(u2), wide = 0.0f;
+    if (fmaxf(fabsf(u1), fabsf(u2)) > 0.125f) {
+        if (fabsf(u1) > 0.125f) h1 = fmaf(A, fast_ln(a1), -df);
+        if (fabsf(u2) > 0.125f) h2 = fmaf(B, fast_ln(b1), df);
+        wide = fabsf(df);
+    }
+    const float rAB = fast_rcp(A * B);
+    float fk = btrs_fc(rAB * B), fnk = btrs_fc(rAB * A);
     if (k < 4) fk = c_fc_tab[k];
     if (n - k < 4) fnk = c_fc_tab[n - k];
     const float f = s.fmn - (fk + fnk);
-    // left-hand side log(v alpha / (aa / us^2 + bb))
-    const float den = fmaf((float)c.aa, fast_rcp(us * us), (float)c.bb);
-    const float lhs = fast_ln((v * s.alpha) * fast_rcp(den));
+    // log((A/M)(B/N)) / 2 less the left-hand side log(v alpha / (aa / us^2 + bb)), as one logarithm
+    // (beyond its range infinite, and undecided)
+    const float us2 = us * us;
+    const float y = fmaf((float)c.bb, us2, (float)c.aa) * fast_rcp((v * s.alpha) * us2);
+    const float lg = 0.5f * fast_ln((a1 * b1) * (y * y));
     const float hs = h1 + h2;
-    const float D = ((fmaf(df, s.L0, hl) - hs) + f) - lhs;
-    const float S = ((hs + (s1 && s2 ? 0.0f : fabsf(df))) + fabsf(df * s.L0)) + (fabsf(lhs) + 1.0f);
+    const float D = (fmaf(df, s.L0, lg) - hs) + f;
+    const float S = ((hs + wide) + fabsf(df * s.L0)) + (fabsf(lg) + 1.0f);
     const float E = fmaf((float)n, 0x1p-41f, 0x1p-17f * S);
     return D > E ? 1 : (D < -E ? -1 : 0);
 }
