@@ -275,6 +275,21 @@ template <typename real> __device__ __forceinline__ real lane_push(real v, int t
     }
 }
 
+// The draws of a SIR or SEIR day of a filter with more waves than chunks of 64 particles, as
+// items: item i is draw b of particles j0 .. j0 + 63, b-major, and wave w of W takes items w, w +
+// W, ...: the day's flows of one particle are drawn on several waves at once.
+template <int MODEL> struct DayItems {
+    int b, j0;
+    __device__ __forceinline__ DayItems(int i, int nx)
+    {
+        const int per = (nx + 63) >> 6;
+        b = (i >= per ? 1 : 0) + (ModelShape<MODEL>::NC > 2 && i >= 2 * per ? 1 : 0);
+        j0 = (i - b * per) << 6;
+    }
+    static __device__ __forceinline__ int count(int nx) { return ModelShape<MODEL>::NC * ((nx + 63) >> 6); }
+    static __device__ __forceinline__ bool spread(int nx) { return (int)(blockDim.x >> 6) > ((nx + 63) >> 6); }
+};
+
 // A particle's probability of leaving S, kept for the day's open draws and score beside the flows:
 // in the fourth row of flows in FP32, in the third and fourth for SIR in FP64. SEIR's three rows of
 // flows leave an FP64 value no room: there it is computed again from the day-start counts.
@@ -313,23 +328,24 @@ template <typename real, int MODEL> struct KeptProb {
 // (256 rejected attempts give the mode). Every attempt is a function of its Philox coordinates
 // alone, so the flows do not depend on the lane that draws them.
 //
-// All lanes active; j0 is the particle of lane 0. Bit d = PER gr + b of a lane's mask stands for
-// the flow out of compartment b of its group gr, gr < n_groups:
-// SIR and SEIR: gr counts passes of blockDim particles; the draws of all passes are settled at
-// once (13 open draws a wave and pass fill a batch only over several: 1000 SEIR filters, N_x =
-// 1000, 150 days, against a batch a pass 5.90 -> 5.29 ms; learned sampler, 4096 filters x 1024 x
-// 150, 79.9 -> 71.3 ms; one pass, with scores, 1.57 -> 1.61). flows[b * cap + j] holds the flows
-// and st the day-start counts; the flow of an open draw is set here.
-// Age-structured: gr is the age group, ps its leave probabilities of S. st already holds the
+// All lanes active. Bit d < count of a lane's mask:
+// SIR and SEIR: draw d % ND of the wave's pass d / ND, first + lane the particle of its first, or
+// where the day's draws are spread (DayItems) the wave's item first + d W. flows[b * cap + j]
+// holds the flows and st the day-start counts; the flow of an open draw is set here. The draws of
+// all passes are settled at once (13 open draws a wave and pass fill a batch only over several:
+// 1000 SEIR filters, N_x = 1000, 150 days, against a batch a pass 5.90 -> 5.29 ms; learned
+// sampler, 4096 filters x 1024 x 150, 79.9 -> 71.3 ms).
+// Age-structured: draw d of particle first + lane, the flow out of compartment d = 3 gr + b; ps
+// are the age groups' leave probabilities of S. st already holds the
 // counts with the settled flows applied and flows[gr * cap + j] the flow out of E, or, while that
 // draw is open, the day-start E. An open S still holds its day-start count; an open I has gained
 // the flow out of E unless that one is open too, which it then still is (descending order).
 template <typename real, int MODEL>
-__device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st, int32_t* flows, int cap, int j0,
-                                            uint32_t open, int n_groups, const real (&ps)[4], DrawStream ds)
+__device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st, int32_t* flows, int cap, int nx,
+                                            int first, uint32_t open, int count, const real (&ps)[4], DrawStream ds)
 {
     constexpr bool AGE = MODEL == MODEL_AGE;
-    constexpr int PER = MODEL == MODEL_SIR ? 2 : 3;
+    constexpr int ND = ModelShape<MODEL>::NC;
     const int lane = lane_id();
     const uint64_t below = lanes_below();
     const uint32_t before = open << 1;  // bit d: draw d - 1 is open
@@ -341,7 +357,7 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
         real ip = (real)0;
         int cnt = 0;
 #pragma nounroll
-        for (int d = PER * n_groups - 1, b = PER - 1, gr = n_groups - 1; d >= 0; --d) {
+        for (int d = count - 1, b = 2, gr = 3; d >= 0; --d) {
             const bool mine = ((open >> d) & 1u) != 0u;
             const uint64_t m = __ballot(mine);
             const int c = __popcll(m);
@@ -359,8 +375,8 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
                 open &= ~(1u << d);
                 cnt += c;
             }
-            gr = b == 0 ? gr - 1 : gr;
-            b = b == 0 ? PER - 1 : b - 1;
+            gr = b == 0 ? gr - 1 : gr;  // age-structured
+            b = b == 0 ? 2 : b - 1;
         }
         const int lr = cnt > 32 ? 0 : (cnt > 16 ? 1 : (cnt > 8 ? 2 : (cnt > 4 ? 3 : (cnt > 2 ? 4 : (cnt > 1 ? 5 : 6)))));
         const int r = 1 << lr, slot = lane >> lr, jj = lane & (r - 1);
@@ -374,9 +390,20 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
         BtrsFinal fs{};
         if (todo) {
             const int d = (int)((id >> 6) & 31u);
-            gr = PER == 2 ? d >> 1 : (d * 11) >> 5;  // d / 3
-            b = d - PER * gr;
-            jo = j0 + (int)(id & 63u) + (AGE ? 0 : gr * (int)blockDim.x);
+            if constexpr (AGE) {
+                gr = (d * 11) >> 5;  // d / 3
+                b = d - 3 * gr;
+                jo = first + (int)(id & 63u);
+            } else {
+                gr = ND == 2 ? d >> 1 : (d * 11) >> 5;  // d / ND
+                b = d - ND * gr;
+                jo = first + (int)(id & 63u) + gr * (int)blockDim.x;
+                if (DayItems<MODEL>::spread(nx)) {
+                    const DayItems<MODEL> it(first + d * (int)(blockDim.x >> 6), nx);
+                    b = it.b;
+                    jo = it.j0 + (int)(id & 63u);
+                }
+            }
             ds.j = (uint32_t)jo;
             ds.b = (uint32_t)(AGE ? d : b);
             from = st + (AGE ? d : b) * cap + jo;
@@ -387,7 +414,7 @@ __device__ __forceinline__ void settle_open(const MConst<real>& mc, int32_t* st,
             } else {
                 p = KeptProb<real, MODEL>::get(mc, st, flows, cap, jo);
             }
-            p = b == 0 ? p : (b == PER - 1 ? mc.p_ir : mc.p_ei);
+            p = b == 0 ? p : (b == (AGE ? 2 : ND - 1) ? mc.p_ir : mc.p_ei);
             flip = p > (real)0.5;
             p = flip ? (real)1 - p : p;
             c = btrs_setup<real>(n, p);
@@ -498,6 +525,25 @@ __device__ __forceinline__ uint32_t particle_draws(const MConst<real>& mc, const
     return open;
 }
 
+// One item of the day's spread draws, the same way.
+template <typename real, int MODEL>
+__device__ __forceinline__ bool item_draw(const MConst<real>& mc, const int32_t* st, int32_t* flows, int cap, int b,
+                                          int j, DrawStream ds)
+{
+    constexpr int ND = ModelShape<MODEL>::NC;
+    real p = b == ND - 1 ? mc.p_ir : mc.p_ei;
+    if (b == 0) {
+        p = leave_prob<real>(mc.cinf * (real)st[(ND - 1) * cap + j]);
+        KeptProb<real, MODEL>::put(flows, cap, j, p);
+    }
+    const double l1p = b == 0 ? NAN : (b == ND - 1 ? mc.l1p_ir : mc.l1p_ei);
+    ds.j = (uint32_t)j;
+    ds.b = (uint32_t)b;
+    bool left;
+    flows[b * cap + j] = binomial_first<real>(st[b * cap + j], p, ds, l1p, b == ND - 1 ? mc.f1_ir : mc.f1_ei, left);
+    return left;
+}
+
 // One day of the linear-Gaussian or the age-structured model for particle j, whose state lives in
 // LDS (st[c * cap + j]); flows drawn from the previous day's state, age group g's with draw
 // index b = 3g, 3g+1, 3g+2 (the compartment that the flow leaves) in a loop: one copy of the
@@ -577,7 +623,7 @@ __device__ __forceinline__ real particle_day(const MConst<real>& mc, int32_t* st
             st[(3 * g + 2) * cap + j] = I + nei - nir;
             flows[g * cap + j] = (open >> (3 * g + 1)) & 1u ? E : nei;
         }
-        settle_open<real, MODEL>(mc, st, flows, cap, j - lane_id(), open, 4, ps, ds);
+        settle_open<real, MODEL>(mc, st, flows, cap, 0, j - lane_id(), open, 12, ps, ds);
         // the observation terms after the draws, four independent chains at once; the
         // day's new cases wait in the weight and gather buffers, free while drawing
         int32_t mu[4];
@@ -1011,19 +1057,32 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
                 __syncthreads();  // any wave may have drawn any particle's flows
                 if (tid == 0) wg_next = 0;  // for the next day (read again only after further barriers)
             } else {
-                // whole waves, each its own particles, as many passes as a mask of open draws holds
-                for (int j = tid; uniform_i32(j) < nx;) {
-                    const int j0 = j - lane_id();
+                const DrawStream ds{0u, filt, kt, 0u, run.k0, run.k1};
+                const real none[4] = {};
+                if (DayItems<MODEL>::spread(nx)) {
+                    const int items = DayItems<MODEL>::count(nx), w0 = uniform_i32(wave_id());
                     uint32_t open = 0;
-                    int np = 0;
-                    for (; np < 32 / NC && uniform_i32(j) < nx; ++np, ++pass, j += nthr)
-                        open |= particle_draws<real, MODEL>(
-                                    mc, st, flows, cap, j, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1},
-                                    pass * G, ptotal)
-                                << (NC * np);
-                    const real none[4] = {};
-                    settle_open<real, MODEL>(mc, st, flows, cap, j0, open, np, none,
-                                             DrawStream{0u, filt, kt, 0u, run.k0, run.k1});
+                    int d = 0;  // at most NC items a wave
+#pragma nounroll
+                    for (int i = w0; i < items; i += nthr >> 6, ++d) {
+                        const DayItems<MODEL> it(i, nx);
+                        open |= (uint32_t)item_draw<real, MODEL>(mc, st, flows, cap, it.b, it.j0 + lane_id(), ds) << d;
+                    }
+                    settle_open<real, MODEL>(mc, st, flows, cap, nx, w0, open, d, none, ds);
+                    __syncthreads();  // any wave may have drawn any particle's flows
+                } else {
+                    // whole waves, each its own particles, as many passes as a mask of open draws holds
+                    for (int j = tid; uniform_i32(j) < nx;) {
+                        const int j0 = j - lane_id();
+                        uint32_t open = 0;
+                        int np = 0;
+                        for (; np < 32 / NC && uniform_i32(j) < nx; ++np, ++pass, j += nthr)
+                            open |= particle_draws<real, MODEL>(
+                                        mc, st, flows, cap, j, DrawStream{(uint32_t)j, filt, kt, 0u, run.k0, run.k1},
+                                        pass * G, ptotal)
+                                    << (NC * np);
+                        settle_open<real, MODEL>(mc, st, flows, cap, nx, j0, open, NC * np, none, ds);
+                    }
                 }
             }
             for (int j = tid; j < nx; j += nthr) {
@@ -1239,24 +1298,30 @@ size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched)
     return bytes;
 }
 
+// The waves that can share a day's draws: SIR's and SEIR's flows of a particle may be drawn by
+// different waves (DayItems), the other models' particles stay with their wave.
+static int day_items(int model, int nx)
+{
+    return ((nx + 63) / 64) * (model == MODEL_SIR ? 2 : (model == MODEL_SEIR ? 3 : 1));
+}
+
 // A launch of at most 512 filters leaves wave slots free with the sizes below: each of the
 // 256 CUs holds one or two filters, four waves each. A filter is then bound by the latency of
 // its days, one after another, so it gets the waves that its share of the CU's 16 (four a
-// SIMD at 128 VGPRs) allows, up to a particle per thread: half of 16 for two filters a CU, all
-// for one. More threads than particles measured slower (16 SIR filters, N_x = 500, pooled:
-// 256 threads 0.54 ms, 512 0.46, 768 0.49, 1024 0.55), as did three filters a CU on more than
-// four waves each (their waves no longer divide over the SIMDs; 700 SEIR filters, N_x = 300:
-// 256 threads 1.67 ms, 320 2.37). Measured, old size -> this: 100 linear-Gaussian filters,
-// N_x = 257, 0.66 -> 0.60 ms; 512 SEIR filters, N_x = 500, 1.91 -> 1.63 ms and with scores
-// 2.41 -> 1.96; 200 age-structured filters, N_x = 700, 5.28 -> 4.34 ms.
+// SIMD at 128 VGPRs) allows, up to an item of draws per wave and beyond 8 waves a particle per
+// thread: half of 16 for two filters a CU, all for one. Measured (per draw): 64 SIR filters, N_x = 64: 64 threads 0.43 ms, 128 0.38, 192
+// 0.39; 100 SEIR filters, N_x = 100: 128 threads 0.86 ms, 192 0.75, 384 0.67; 16 SIR filters, N_x =
+// 500: 256 threads 0.44 ms, 512 0.36, 1024 0.38; three filters a CU on more than four waves each
+// (their waves no longer divide over the SIMDs): 700 SEIR filters, N_x = 300, 256 threads 1.6 ms,
+// 320 1.9. Against 256 threads: 100 linear-Gaussian filters, N_x = 257, 0.66 -> 0.60 ms; 512 SEIR
+// filters with scores, N_x = 500, 1.94 -> 1.60; 200 age-structured filters, N_x = 700, 5.28 -> 4.34.
 static int pf_few_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
 {
-    const int per_cu = n_filters <= 256 ? 1 : 2;
-    const int full = ((nx + 63) / 64) * 64;
-    const int most = full < 1024 / per_cu ? full : 1024 / per_cu;
-    for (int b = most; 2 * b >= most && b >= 64; b -= 64) {
-        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
-        if (sc >= 0 && pf_lds_bytes(model, prec, b, nx, T, sc) * per_cu <= PF_LDS_MAX) return b;
+    const int per_cu = n_filters <= 256 ? 1 : 2, full = (nx + 63) / 64, items = day_items(model, nx);
+    const int most = items < 8 ? items : (full > 8 ? full : 8);
+    for (int w = most < 16 / per_cu ? most : 16 / per_cu; w >= 1; --w) {
+        const int sc = pf_pick_schedule(model, prec, 64 * w, nx, T, requested_sched, score);
+        if (sc >= 0 && pf_lds_bytes(model, prec, 64 * w, nx, T, sc) * per_cu <= PF_LDS_MAX) return 64 * w;
     }
     return 0;
 }
@@ -1279,12 +1344,12 @@ static int pf_few_filters_block(int model, int prec, int nx, int T, int requeste
 static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
 {
     static const int sizes[] = {64, 128, 192, 256, 512, 1024};
-    const int full = ((nx + 63) / 64) * 64;
+    const int items = day_items(model, nx), full = ((nx + 63) / 64) * 64;
     const auto pass_time = [](double waves) { return 0.46 + 0.54 * waves / 16.0; };
     int best = 0;
     double best_time = 0.0;
     for (int b : sizes) {
-        if (b > full) break;
+        if (b > 64 * items) break;
         const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
         if (sc < 0) continue;
         const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
@@ -1293,10 +1358,15 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
         const int rounds = n_filters / (256 * per_cu), last = (n_filters - rounds * 256 * per_cu + 255) / 256;
         double time = rounds * pass_time(per_cu * w) + (last > 0 ? pass_time(last * w) : 0.0);
         const bool several = n_filters > 256 * per_cu;
+        // spread draws shorten a day, they take no work off a full CU (4096 filters, N_x = 300, 60
+        // days: 512 threads 4.84 ms, 128 3.83)
+        if (several && b > full) continue;
         if (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED) {
-            time *= (0.75 + 0.68 * nx / b) * (several ? 1.05 : 1.0);  // its waves share the passes
+            time *= (double)nx / b * (several ? 1.15 : 1.0);
         } else {
-            const double mean = (double)(full / 64) / w, most = (double)((nx + b - 1) / b);
+            // in draws: single ones where they are spread, else a particle's all
+            const int flows = 64 * items / full;
+            const double mean = (double)items / w, most = b > full ? (items + w - 1) / w : flows * ((nx + b - 1) / b);
             time *= (mean + 0.6 * (most - mean)) * (several ? (w == 1 ? 1.03 : 1.15) : 1.0);
         }
         if (best == 0 || time < best_time) {
@@ -1316,10 +1386,10 @@ int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bo
         if (b > 0) return b;
     }
     // launches of runs of different sizes: the workgroup size that keeps the most waves resident
-    // per CU (LDS allowing, at most 16 at 128 VGPRs), preferring the pooled schedule where it is taken
+    // per CU (LDS allowing, at most 16 at 128 VGPRs)
     const int full = ((nx + 63) / 64) * 64;
     int best = full < 256 ? full : 256;
-    double best_score = -1.0;
+    int best_waves = -1;
     for (int b = best; b <= 1024; b *= 2) {
         const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
         if (sc < 0) continue;
@@ -1328,9 +1398,8 @@ int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bo
         const int per_cu = (int)(PF_LDS_MAX / (lds ? lds : 1));
         int waves = per_cu * (b / 64);
         waves = waves > 16 ? 16 : waves;
-        const double merit = waves * (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED ? 1.4 : 1.0);
-        if (merit > best_score + 1e-9) {
-            best_score = merit;
+        if (waves > best_waves) {
+            best_waves = waves;
             best = b;
         }
         if (b >= full) break;
@@ -1355,12 +1424,10 @@ int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requeste
                            pf_lds_bytes(model, prec, block, nx, T, PF_SCHED_POOLED) <= PF_LDS_MAX;
     if (requested == PF_SCHED_PER_DRAW) return PF_SCHED_PER_DRAW;
     if (requested == PF_SCHED_POOLED) return pooled_ok ? PF_SCHED_POOLED : -1;
-    // automatic: per draw, but for two passes of 256 threads with the second partly filled, which
-    // the pooled schedule spreads over all waves (SEIR, 100 days, pooled against per draw: 700
-    // filters, N_x = 300, 1.50 against 1.64 ms; 1000, N_x = 333, 1.81 against 1.90; N_x = 257, 1.66
-    // against 1.56; N_x = 512, 2.15 against 2.12; N_x = 1000, 4.45 against 3.86)
-    const bool ragged = block == 256 && nx >= 288 && nx < 448;
-    return pooled_ok && ragged ? PF_SCHED_POOLED : PF_SCHED_PER_DRAW;
+    // automatic: per draw (SEIR against pooled: 1000 filters, N_x = 1000, 150 days, 5.15 against 6.65
+    // ms; N_x = 333, 100 days, 1.80 against 1.82; 2048, N_x = 300, 60 days, 1.68 against 2.32; 4096,
+    // N_x = 1024, 150 days, 20.9 against 24.5)
+    return PF_SCHED_PER_DRAW;
 }
 
 template <typename real, int MODEL, int OBS, int SCHED>

@@ -157,3 +157,23 @@ def test_open_draws_of_many_passes(preset, nx, prec):
     y = np.full((5, 1), 12, dtype=np.int32)
     theta = np.tile(truth, (3, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (3, w["D"])))
     _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW, block=64)
+
+
+@pytest.mark.parametrize("block", [64, 128, 192, 256, 448, 1024])
+@pytest.mark.parametrize("preset,nx", [("sir_fp64", 60), ("sir_fp64", 130), ("seir", 64), ("seir", 130)])
+def test_flows_of_one_particle_on_several_waves(preset, nx, block):
+    """Workgroups of fewer, as many and more waves than the particles fill, up to more than
+    there are draws of 64 particles: the flows of a day drawn in place or spread."""
+    w = dict(W.preset(preset), n_pop=4000.0, T=6)
+    truth = np.array(w["truth"])
+    if preset == "sir_fp64":
+        w["fixed"], truth[1] = [120], 0.12
+    else:
+        truth[1:4] = 0.12, 0.15, 0.025
+    y = np.full((6, 1), 12, dtype=np.int32)
+    theta = np.tile(truth, (4, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (4, w["D"])))
+    for prec in (G.PREC_FP32, G.PREC_FP64):
+        _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW, block=block)
+    a, sa = G.pf_score(w, theta, y, nx, 9, 2, block=block)
+    b, sb = G.pf_score(w, theta, y, nx, 9, 2, block=64)
+    assert np.array_equal(a, b) and np.array_equal(sa, sb)
