@@ -57,7 +57,8 @@ VALU_PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # VALU-busy fraction (SQ_ACTIVE_INST_VALU / 256 CUs / (GRBM_GUI_ACTIVE / 8 XCDs): cycles
 # in which the VALU issued, whatever the lanes). A changed kernel reports them as null.
 KERNEL_SOURCES = ["paper_2311_12973_amd/csrc/pf_kernel.hip", "paper_2311_12973_amd/csrc/pf_kernel.h",
-                  "paper_2311_12973_amd/csrc/device_common.h", "paper_2311_12973_amd/csrc/block_ops.h",
+                  "paper_2311_12973_amd/csrc/device_common.h", "paper_2311_12973_amd/csrc/fast_fp64.h",
+                  "paper_2311_12973_amd/csrc/block_ops.h",
                   "paper_2311_12973_amd/build.py"]
 MEASURED = {
     "age_seir": dict(sha="44d6452744a009f5", valu_lane_instr_per_pstep=2397.1, hbm_bytes_per_launch=10341702729,
