@@ -264,9 +264,9 @@ __device__ __forceinline__ double lfact(double x)
 // n p + 1/2 split in FP64 into integer and fraction; the final acceptance test is
 // defined in FP64 on log-factorials (btrs_final) and decided FP32-first with an error
 // bound (btrs_final_fast, btrs_decide). Attempt e uses words 2(e&1), 2(e&1)+1 of call e>>1.
-// The three pieces below are shared by the per-draw sampler (binom_btrs) and the
-// particle filter's pooled schedule, which defers final tests; both take identical
-// decisions because each piece is a pure function of (n, p, k, words).
+// The pieces below are shared by the sequential sampler (binom_btrs), the filter's per-draw
+// schedule (btrs_first, then the wave's open draws) and its pooled one, which defers final
+// tests; all take identical decisions because each piece is a pure function of (n, p, k, words).
 template <typename real> struct BtrsConst {
     real spq, bb, aa, vr, cf;
     int32_t ci;
