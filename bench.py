@@ -62,11 +62,11 @@ KERNEL_SOURCES = ["paper_2311_12973_amd/csrc/pf_kernel.hip", "paper_2311_12973_a
                   "paper_2311_12973_amd/csrc/block_ops.h",
                   "paper_2311_12973_amd/build.py"]
 MEASURED = {
-    "age_seir": dict(sha="f4a9370629f20e9a", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=130697308,
-                     valu_busy=1.0259,
+    "age_seir": dict(sha="c9bef2e7af3691b4", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=129687745,
+                     valu_busy=1.0254,
                      profile="profiles/pf_kernel_age_seir_n16384_nx2048_t365.txt"),
-    "seir": dict(sha="f4a9370629f20e9a", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1123094,
-                 valu_busy=1.13,
+    "seir": dict(sha="c9bef2e7af3691b4", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1122831,
+                 valu_busy=1.1296,
                  profile="profiles/pf_kernel_seir_n1024_nx512_t100.txt"),
 }
 

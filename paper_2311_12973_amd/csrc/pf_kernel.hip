@@ -1319,7 +1319,9 @@ static int pf_few_filters_block(int model, int prec, int nx, int T, int requeste
 {
     const int per_cu = n_filters <= 256 ? 1 : 2, full = (nx + 63) / 64, items = day_items(model, nx);
     const int most = items < 8 ? items : (full > 8 ? full : 8);
-    for (int w = most < 16 / per_cu ? most : 16 / per_cu; w >= 1; --w) {
+    const int start = most < 16 / per_cu ? most : 16 / per_cu;
+    // not below half of it: two narrow filters a CU are no match for one on all its waves
+    for (int w = start; 2 * w >= start; --w) {
         const int sc = pf_pick_schedule(model, prec, 64 * w, nx, T, requested_sched, score);
         if (sc >= 0 && pf_lds_bytes(model, prec, 64 * w, nx, T, sc) * per_cu <= PF_LDS_MAX) return 64 * w;
     }
