@@ -1410,6 +1410,13 @@ int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bo
         }
         if (b >= full) break;
     }
+    // none of these sizes fits: the widest that does, so that whether a shape is accepted depends
+    // neither on the number of filters nor on the sizes preferred for it (SEIR scores at N_x =
+    // 2150 fit in rows of 2176 particles, not of 2304)
+    for (int b = 1024; best_waves < 0 && b >= 64; b -= 64) {
+        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
+        if (sc >= 0 && pf_lds_bytes(model, prec, b, nx, T, sc) <= PF_LDS_MAX) return b;
+    }
     return best;
 }
 

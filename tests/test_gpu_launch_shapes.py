@@ -35,3 +35,23 @@ def test_workgroup_sizes_that_round_the_particles_beyond_4096(preset, prec, nx, 
     assert np.isfinite(b[0]).all()
     for u, v in zip(a, b):
         assert np.array_equal(u, v)
+
+
+def test_shapes_at_the_end_of_lds_run_for_every_number_of_filters():
+    """SEIR scores at N_x = 2150 fit in rows of 2176 particles only: accepted for few and for many
+    filters and for a context of several runs, with the same results."""
+    w, y, theta = _case("seir", 513, 3)
+    want, want_s = G.pf_score(w, theta, y, 2150, 3, 1, block=64)
+    for n in (1, 512, 513):
+        print("end of LDS", n, flush=True)
+        a, s = G.pf_score(w, theta[:n], y, 2150, 3, 1)
+        assert np.array_equal(a, want[:n]) and np.array_equal(s, want_s[:n])
+    runs = [dict(T=3, nx=2150, seed=i + 1, y=y) for i in range(2)]
+    recs = []
+    for block in (0, 64):
+        s = G.Sampler(w, runs, N=32, K=2, proposal=G.PROP_LANGEVIN, block=block)
+        for _ in range(2):
+            s.step()
+        recs.append([s.records(r) for r in range(2)])
+        s.close()
+    assert np.array_equal(recs[0], recs[1])
