@@ -1332,55 +1332,91 @@ static int pf_few_filters_block(int model, int prec, int nx, int T, int requeste
     return 0;
 }
 
-// Larger launches: the workgroup size of the least estimated time, in units of a pass over a
-// workgroup's particles with all 16 wave slots of a CU taken. What enters, each fitted to one
-// series of measurements (SEIR, per draw) and then right, or within 2%, at 45 of 48 others (SEIR
-// with and without scores, FP64 SIR, linear-Gaussian and age-structured, 700 to 12288 filters,
-// N_x = 100 to 2000; the other three within 9%):
-//  - a pass with W resident waves takes 0.46 + 0.54 W / 16 (1000 filters, N_x = 512: 4, 8, 16
-//    waves a CU take 8, 4, 2 passes in 5.04, 3.09, 2.12 ms): narrow workgroups serve the launch
-//    whose filters are all resident, wide ones the one of few filters;
-//  - a wave with a pass more than the average holds up its workgroup for 0.6 of the difference
-//    (the other workgroups of the CU fill in the rest);
-//  - filters beyond those resident at once (by LDS and wave slots) wait for the next round, and
-//    the workgroups of several rounds fall out of step: 15% more, 3% for a single wave, which
-//    never waits at a barrier.
-// Against the size before (the most waves resident, at least 256 threads): 2048 filters, N_x =
-// 512, 60 days 2.93 -> 2.52 ms; 4096, N_x = 128, 1.87 -> 1.36 ms; 3000, N_x = 257, 3.10 -> 2.41.
+// Workgroups of `waves` waves and `lds` bytes (and the kernel's few static ones) that a CU holds at
+// once: 16 wave slots (four a SIMD at 128 VGPRs), and LDS in granules of 1280 bytes (64 threads and
+// 15872 bytes: the time of a launch jumps beyond 9 workgroups a CU, not 10).
+static int pf_resident(size_t lds, int waves)
+{
+    constexpr size_t granule = 1280;
+    const int by_lds = (int)(160 * 1024 / ((lds + 16 + granule - 1) / granule * granule)), by_waves = 16 / waves;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
+// The workgroup size, 256 (or N_x) doubled, that keeps the most waves resident per CU by its LDS; 0
+// when none fits.
+static int pf_most_waves_block(int model, int prec, int nx, int T, int requested_sched, bool score)
+{
+    const int full = ((nx + 63) / 64) * 64;
+    int best = 0, best_waves = -1;
+    for (int b = full < 256 ? full : 256; b <= 1024; b *= 2) {
+        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
+        if (sc >= 0) {
+            const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
+            const int waves = lds <= PF_LDS_MAX ? (int)(PF_LDS_MAX / lds) * (b / 64) : -1;
+            if ((waves < 16 ? waves : 16) > best_waves) {
+                best_waves = waves < 16 ? waves : 16;
+                best = b;
+            }
+        }
+        if (b >= full) break;
+    }
+    return best;
+}
+
+// Larger launches: the workgroup size of the least estimated time, in units of a pass over
+// a workgroup's particles with all 16 wave slots of a CU taken, where that saves 7% against the
+// size of the most resident waves; else that size. What enters the estimate:
+//  - a pass with s of a SIMD's four wave slots taken takes 0.5 + 0.5 s / 4;
+//  - a wave with a pass more than the average holds up its workgroup for a quarter of the
+//    difference (the other workgroups of the CU fill in the rest); spread draws for all of it,
+//    pooled ones, which the waves share, for none;
+//  - filters beyond those resident at once wait for the next round, and then the rest of a day
+//    (weights, sums, resampling), which every wave runs once whatever its passes, adds 0.7 s / 4
+//    a round, 0.2 beside the age-structured model's twelve draws. It speaks against rounds of
+//    wide workgroups (600 linear-Gaussian filters, N_x = 1000, 200 days: three rounds of 1024
+//    threads 3.49 ms, one of 256 2.17; 2500, N_x = 512: 512 threads 1.05, 256 0.79).
+// Over 1955 launches per draw (the four models, SEIR and SIR in both precisions, SEIR and
+// linear-Gaussian with scores, 513 to 12288 filters, N_x = 40 to 4096) the size taken is 0.4% slower
+// than the fastest of nine in the geometric mean, 3% at the 95th percentile and 16% at most; the
+// most resident waves alone 5%, 31% and 57%. Over 1225 pooled ones 1.6%, 12% and 32%; 6%, 31%, 54%.
 static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
 {
     static const int sizes[] = {64, 128, 192, 256, 512, 1024};
-    const int items = day_items(model, nx), full = ((nx + 63) / 64) * 64;
-    const auto pass_time = [](double waves) { return 0.46 + 0.54 * waves / 16.0; };
+    const int chunks = (nx + 63) / 64, items = day_items(model, nx), flows = items / chunks;
+    const double day = model == MODEL_AGE ? 0.2 : 0.7;
+    // 0: the size does not fit, or spreads draws over the waves of a full CU, which shortens a day but
+    // takes no work off it (4096 filters, N_x = 300, 60 days: 512 threads 4.84 ms, 128 3.83)
+    const auto estimate = [&](int b) {
+        const int w = b / 64, sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
+        if (sc < 0) return 0.0;
+        const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
+        if (lds > PF_LDS_MAX) return 0.0;
+        const int per_cu = pf_resident(lds, w), round = 256 * per_cu;
+        const bool several = n_filters > round;
+        if (w > chunks && several) return 0.0;
+        const double mean = (double)chunks / w;
+        const double passes = sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED ? (double)nx / b
+                              : w > chunks ? (double)((items + w - 1) / w) / flows
+                                           : mean + 0.25 * ((chunks + w - 1) / w - mean);
+        const auto time = [&](int groups) {
+            const double s = (groups * w + 3) / 4 / 4.0;
+            return passes * (0.5 + 0.5 * s) + (several ? day * s : 0.0);
+        };
+        const int rounds = n_filters / round, last = (n_filters - rounds * round + 255) / 256;
+        return rounds * time(per_cu) + (last > 0 ? time(last) : 0.0);
+    };
     int best = 0;
     double best_time = 0.0;
     for (int b : sizes) {
-        if (b > 64 * items) break;
-        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
-        if (sc < 0) continue;
-        const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
-        if (lds > PF_LDS_MAX) continue;
-        const int w = b / 64, by_lds = (int)(PF_LDS_MAX / lds), per_cu = by_lds < 16 / w ? by_lds : 16 / w;
-        const int rounds = n_filters / (256 * per_cu), last = (n_filters - rounds * 256 * per_cu + 255) / 256;
-        double time = rounds * pass_time(per_cu * w) + (last > 0 ? pass_time(last * w) : 0.0);
-        const bool several = n_filters > 256 * per_cu;
-        // spread draws shorten a day, they take no work off a full CU (4096 filters, N_x = 300, 60
-        // days: 512 threads 4.84 ms, 128 3.83)
-        if (several && b > full) continue;
-        if (sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED) {
-            time *= (double)nx / b * (several ? 1.15 : 1.0);
-        } else {
-            // in draws: single ones where they are spread, else a particle's all
-            const int flows = 64 * items / full;
-            const double mean = (double)items / w, most = b > full ? (items + w - 1) / w : flows * ((nx + b - 1) / b);
-            time *= (mean + 0.6 * (most - mean)) * (several ? (w == 1 ? 1.03 : 1.15) : 1.0);
-        }
-        if (best == 0 || time < best_time) {
+        const double time = b <= 64 * items ? estimate(b) : 0.0;
+        if (time > 0.0 && (best == 0 || time < best_time)) {
             best = b;
             best_time = time;
         }
     }
-    return best;
+    const int usual = pf_most_waves_block(model, prec, nx, T, requested_sched, score);
+    const double usual_time = usual > 0 ? estimate(usual) : 0.0;
+    return best == 0 || (usual_time > 0.0 && best_time > 0.93 * usual_time) ? usual : best;
 }
 
 int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
@@ -1391,33 +1427,17 @@ int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bo
                           : pf_many_filters_block(model, prec, nx, T, requested_sched, score, n_filters);
         if (b > 0) return b;
     }
-    // launches of runs of different sizes: the workgroup size that keeps the most waves resident
-    // per CU (LDS allowing, at most 16 at 128 VGPRs)
-    const int full = ((nx + 63) / 64) * 64;
-    int best = full < 256 ? full : 256;
-    int best_waves = -1;
-    for (int b = best; b <= 1024; b *= 2) {
-        const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
-        if (sc < 0) continue;
-        const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
-        if (lds > PF_LDS_MAX) continue;
-        const int per_cu = (int)(PF_LDS_MAX / (lds ? lds : 1));
-        int waves = per_cu * (b / 64);
-        waves = waves > 16 ? 16 : waves;
-        if (waves > best_waves) {
-            best_waves = waves;
-            best = b;
-        }
-        if (b >= full) break;
-    }
+    // launches of runs of different sizes
+    const int usual = pf_most_waves_block(model, prec, nx, T, requested_sched, score);
+    if (usual > 0) return usual;
     // none of these sizes fits: the widest that does, so that whether a shape is accepted depends
     // neither on the number of filters nor on the sizes preferred for it (SEIR scores at N_x =
     // 2150 fit in rows of 2176 particles, not of 2304)
-    for (int b = 1024; best_waves < 0 && b >= 64; b -= 64) {
+    for (int b = 1024; b >= 64; b -= 64) {
         const int sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
         if (sc >= 0 && pf_lds_bytes(model, prec, b, nx, T, sc) <= PF_LDS_MAX) return b;
     }
-    return best;
+    return 256;
 }
 
 int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requested, bool score)

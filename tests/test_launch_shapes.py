@@ -29,3 +29,25 @@ def test_a_shape_is_accepted_whatever_the_number_of_filters(preset, prec, score,
         rc = (L.smc2_pf_score(ctypes.byref(c), n, fake, runs, 1, fake, fake, fake, ws, None) if score else
               L.smc2_pf_loglik(ctypes.byref(c), n, fake, runs, 1, fake, fake, ws, None))
         assert rc == (G.E_DEVICE if fits else G.E_ARG), (n, L.smc2_last_error(None))
+
+
+def _default_block(model, prec, nx, T, n_filters, schedule=G.SCHED_AUTO, score=False):
+    f = G.lib()._ZN4smc216pf_default_blockEiiiiibi
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_bool, ctypes.c_int]
+    return f(model, prec, nx, T, schedule, score, n_filters)
+
+
+@pytest.mark.parametrize("model,prec,score,n,nx,T,fastest", [
+    # rounds of wide workgroups against one of narrower ones: the rest of a day counts each round
+    (G.LINGAUSS, G.PREC_FP64, False, 600, 1000, 200, 256), (G.LINGAUSS, G.PREC_FP64, False, 1200, 1000, 200, 256),
+    (G.LINGAUSS, G.PREC_FP64, False, 2500, 512, 200, 256), (G.LINGAUSS, G.PREC_FP64, True, 3500, 512, 200, 256),
+    (G.SEIR, G.PREC_FP32, False, 700, 1000, 60, 256), (G.SIR, G.PREC_FP64, False, 513, 1024, 60, 256),
+    # a workgroup more per CU by the bytes of LDS than by its granules
+    (G.SEIR, G.PREC_FP32, False, 2500, 400, 60, 256), (G.SIR, G.PREC_FP64, False, 2500, 400, 60, 256),
+    (G.AGE_SEIR, G.PREC_FP32, False, 1200, 640, 40, 512), (G.AGE_SEIR, G.PREC_FP32, False, 513, 640, 40, 512),
+    # sizes other than the most resident waves'
+    (G.SEIR, G.PREC_FP32, False, 4096, 128, 60, 64), (G.SEIR, G.PREC_FP32, False, 3000, 257, 60, 64),
+    (G.SEIR, G.PREC_FP32, False, 513, 40, 60, 192), (G.SIR, G.PREC_FP32, False, 600, 100, 60, 256)])
+def test_many_filters_take_the_size_that_measured_fastest(model, prec, score, n, nx, T, fastest):
+    """Shapes where the sizes' times lie far apart (10% to 60%): the fastest of those measured."""
+    assert _default_block(model, prec, nx, T, n, score=score) == fastest
