@@ -21,6 +21,10 @@ template <typename real> __device__ __forceinline__ real* red_max_slot(RedLds* r
 template <> __device__ __forceinline__ float* red_max_slot<float>(RedLds* r) { return r->max_f; }
 template <> __device__ __forceinline__ double* red_max_slot<double>(RedLds* r) { return r->max_d; }
 
+// The reductions and scans below join the waves' results in a second step; a workgroup of one wave
+// is done after the first (4483 linear-Gaussian filters, N_x = 32, 150 days: 0.916 ms with the second
+// step, 0.873 without).
+
 // Maximum over the block (exact, order-free).
 template <typename real> __device__ __forceinline__ real block_max(real v, RedLds* red)
 {
@@ -28,8 +32,9 @@ template <typename real> __device__ __forceinline__ real block_max(real v, RedLd
     v = wave_max(v);
     if (lane_id() == 0) slot[wave_id()] = v;
     __syncthreads();
-    // every wave reads the slots into its first lanes and reduces them there
     const int nw = (int)(blockDim.x >> 6);
+    if (nw == 1) return uniform_real<real>(v);
+    // every wave reads the slots into its first lanes and reduces them there
     const real m = slot[lane_id() < nw ? lane_id() : 0];
     return uniform_real<real>(row_reduce(m, [](real x, real u) { return u > x ? u : x; }));
 }
@@ -45,6 +50,11 @@ __device__ __forceinline__ void block_sum_u64(uint64_t& a, uint64_t& b, RedLds* 
     }
     __syncthreads();
     const int nw = (int)(blockDim.x >> 6), l = lane_id() < nw ? lane_id() : 0;
+    if (nw == 1) {
+        a = uniform_u64(a);
+        b = uniform_u64(b);
+        return;
+    }
     const auto add = [](uint64_t x, uint64_t u) { return x + u; };
     const uint64_t sa = red->sum_a[l], sb = red->sum_b[l];
     a = uniform_u64(row_reduce(lane_id() < nw ? sa : 0ull, add));
@@ -92,6 +102,10 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t& total,
     __syncthreads();
     // every wave scans the slots in its first row: the total, and its own offset
     const int nw = (int)(blockDim.x >> 6), me = uniform_i32(wave_id());
+    if (nw == 1) {
+        total = lane_u64(incl, 63);
+        return incl - v;
+    }
     const uint64_t slot = red->scan[lane_id() < nw ? lane_id() : 0];
     const uint64_t own = lane_id() < nw ? slot : 0ull;
     const uint64_t to = row_incl_scan(own);
