@@ -302,7 +302,9 @@ static hipError_t set_launch(smc2_ctx* c, PFGroup& gr)
 
 // Autotuner: for every launch group, time each candidate (workgroup size, draw
 // schedule, persistent or one-filter-per-workgroup grid) on a sample of the group's
-// filters at the first iteration's parameters (prior draws) and keep the fastest.
+// filters at the first iteration's parameters (prior draws) and keep the fastest. The group's
+// untuned size is a candidate too (the defaults for few filters are no powers of two and wider than
+// N_x), so the choice is never slower than the default on the sample.
 // Results do not depend on the choice (every draw is a function of its coordinates),
 // only the time does. Leaves the sampler state as smc2_init found it (k = 0).
 static hipError_t autotune(smc2_ctx* c)
@@ -322,19 +324,24 @@ static hipError_t autotune(smc2_ctx* c)
     const std::vector<int32_t>& host_items = c->host_items;
     for (PFGroup& gr : c->groups) {
         if (e != hipSuccess) break;
-        // sample: about two resident waves of workgroups, strided over the cost-sorted list
+        // sample: about two resident waves of workgroups, strided over the cost-sorted list, or a group
+        // of up to twice as many whole (a narrower candidate may hold all of such a sample at once,
+        // but not all of the group)
         int per_cu = 1;
         e = pf_occupancy(cfg.precision, cfg.model, cfg.obs, gr.sched, gr.block, gr.lds, &per_cu);
         if (e != hipSuccess) break;
-        const int S = std::min(gr.n_items, std::max(64, 2 * std::max(per_cu, 1) * std::max(c->n_cu, 1)));
+        const int two = std::max(64, 2 * std::max(per_cu, 1) * std::max(c->n_cu, 1));
+        const int S = gr.n_items <= 2 * two ? gr.n_items : two;
         std::vector<int32_t> sample(S);
         for (int i = 0; i < S; ++i) sample[i] = host_items[gr.first_item + (int)((long)i * gr.n_items / S)];
         e = hipMemcpyAsync(d_tune, sample.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s);
         PFGroup best = gr;
         float best_ms = -1.f;
         const int full = ((gr.max_nx + 63) / 64) * 64;
-        for (int b = 64; b <= 1024 && e == hipSuccess; b *= 2) {
-            if (b > std::max(64, full)) break;
+        std::vector<int> sizes{gr.block};
+        for (int b = 64; b <= std::min(full, 1024); b *= 2)
+            if (b != gr.block) sizes.push_back(b);
+        for (int b : sizes) {
             for (int sc = PF_SCHED_PER_DRAW; sc <= PF_SCHED_SCORE_POOLED && e == hipSuccess; ++sc) {
                 // the Langevin proposal's launches carry the scores: only those variants
                 const bool sc_score = sc == PF_SCHED_SCORE || sc == PF_SCHED_SCORE_POOLED;
@@ -344,7 +351,9 @@ static hipError_t autotune(smc2_ctx* c)
                     (sc_pooled ? SMC2_SCHED_POOLED : SMC2_SCHED_PER_DRAW) != cfg.schedule)
                     continue;
                 if (sc_pooled && cfg.model != SMC2_SIR && cfg.model != SMC2_SEIR) continue;
-                const size_t lds = pf_lds_bytes(cfg.model, cfg.precision, b, gr.max_nx, gr.max_T, sc);
+                const size_t lds = b == gr.block && sc == gr.sched
+                                       ? gr.lds
+                                       : pf_lds_bytes(cfg.model, cfg.precision, b, gr.max_nx, gr.max_T, sc);
                 if (lds > PF_LDS_MAX) continue;
                 e = pf_prepare(cfg.precision, cfg.model, cfg.obs, sc, lds);
                 for (int pers = 0; pers <= 1 && e == hipSuccess; ++pers) {

@@ -55,3 +55,19 @@ def test_shapes_at_the_end_of_lds_run_for_every_number_of_filters():
         recs.append([s.records(r) for r in range(2)])
         s.close()
     assert np.array_equal(recs[0], recs[1])
+
+
+def test_autotuner_times_the_default_size_too():
+    """64 SEIR filters of 100 particles run by default on 384 threads, six waves for two chunks of
+    particles, a quarter faster than on the 64 or 128 that N_x fills: the autotuner keeps such a size."""
+    w, y, _ = _case("seir", 2, 60)
+    kw = dict(N=64, K=2)
+    runs = [dict(T=60, nx=100, seed=1, y=y)]
+    a, b = G.Sampler(w, runs, **kw), G.Sampler(w, runs, tune=1, **kw)
+    print("tuned", b.groups(), "default", a.groups(), flush=True)
+    assert a.groups()[0]["block"] == 384 and b.groups()[0]["block"] == 384
+    for s in (a, b):
+        s.step()
+    assert np.array_equal(a.records(), b.records())
+    a.close()
+    b.close()
