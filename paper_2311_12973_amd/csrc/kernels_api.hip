@@ -234,9 +234,10 @@ static int pf_run(const smc2_config* cfg, int32_t n_theta, const double* d_theta
         return kfail(SMC2_E_ARG, "block must be 0 or a multiple of 64 up to 1024");
     if (cfg->schedule < 0 || cfg->schedule > 2) return kfail(SMC2_E_ARG, "schedule must be 0, 1 or 2");
     const int want = cfg->schedule;
+    const int n_cu = pf_device_cus();
     const int block =
         cfg->block ? cfg->block
-                   : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, want, score, n_theta);
+                   : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, want, score, n_theta, n_cu);
     const int sched = pf_pick_schedule(cfg->model, cfg->precision, block, run->n_x, run->T, want, score);
     if (sched < 0) return kfail(SMC2_E_ARG, "the pooled schedule cannot run this model, n_x and T");
     const size_t lds = pf_lds_bytes(cfg->model, cfg->precision, block, run->n_x, run->T, sched);
@@ -279,10 +280,8 @@ static int pf_run(const smc2_config* cfg, int32_t n_theta, const double* d_theta
     for (int i = 0; i < SMC2_NFIXED; ++i) a.fx[i] = i < cfg->n_fixed ? cfg->fixed[i] : 0.0;
     if (e == hipSuccess) e = pf_prepare(cfg->precision, cfg->model, cfg->obs, sched, lds);
     // wave priorities when every filter is resident at once (they even out its tail)
-    int per_cu = 0, n_cu = 0, dev = 0;
+    int per_cu = 0;
     if (e == hipSuccess) e = pf_occupancy(cfg->precision, cfg->model, cfg->obs, sched, block, lds, &per_cu);
-    if (e == hipSuccess) e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess && (long)n_theta <= (long)per_cu * n_cu)
         a.prio_scale = (float)(1.0 / ((double)run->T * (double)run->n_x));
     if (e == hipSuccess) e = launch_pf(cfg->precision, cfg->model, cfg->obs, sched, block, lds, a, s);

@@ -73,8 +73,10 @@ size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched);
 // the pooled schedule was requested but cannot run, or the model has no score.
 int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requested, bool score = false);
 // Default workgroup size for a filter of this shape (64 .. 1024 threads), in a launch of
-// n_filters filters of that shape (0: many, or of several shapes).
-int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters);
+// n_filters filters of that shape (0: of several shapes) on a device of n_cu CUs.
+int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters, int n_cu);
+// CUs of the current device (a partition has fewer than the card's 256).
+int pf_device_cus();
 bool pf_supported(int model, int obs);
 // Raise the dynamic-LDS limit of the kernel when a launch needs more than 64 KiB.
 hipError_t pf_prepare(int prec, int model, int obs, int sched, size_t lds);

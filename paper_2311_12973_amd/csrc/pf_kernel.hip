@@ -1309,19 +1309,20 @@ static int day_items(int model, int nx)
     return ((nx + 63) / 64) * (model == MODEL_SIR ? 2 : (model == MODEL_SEIR ? 3 : 1));
 }
 
-// A launch of at most 512 filters leaves wave slots free with the sizes below: each of the
-// 256 CUs holds one or two filters, four waves each. A filter is then bound by the latency of
-// its days, one after another, so it gets the waves that its share of the CU's 16 (four a
-// SIMD at 128 VGPRs) allows, up to an item of draws per wave and beyond 8 waves a particle per
-// thread: half of 16 for two filters a CU, all for one. Measured (per draw): 64 SIR filters, N_x = 64: 64 threads 0.43 ms, 128 0.38, 192
-// 0.39; 100 SEIR filters, N_x = 100: 128 threads 0.86 ms, 192 0.75, 384 0.67; 16 SIR filters, N_x =
-// 500: 256 threads 0.44 ms, 512 0.36, 1024 0.38; three filters a CU on more than four waves each
-// (their waves no longer divide over the SIMDs): 700 SEIR filters, N_x = 300, 256 threads 1.6 ms,
-// 320 1.9. Against 256 threads: 100 linear-Gaussian filters, N_x = 257, 0.66 -> 0.60 ms; 512 SEIR
+// A launch of at most two filters a CU leaves wave slots free with the sizes below, four waves each.
+// A filter is then bound by the latency of its days, one after another, so it gets the waves that
+// its share of the CU's 16 (four a SIMD at 128 VGPRs) allows, up to an item of draws per wave and
+// beyond 8 waves a particle per thread: half of 16 for two filters a CU, all for one. Measured on
+// 256 CUs (per draw): 64 SIR filters, N_x = 64: 64 threads 0.43 ms, 128 0.38, 192 0.39; 100 SEIR
+// filters, N_x = 100: 128 threads 0.86 ms, 192 0.75, 384 0.67; 16 SIR filters, N_x = 500: 256
+// threads 0.44 ms, 512 0.36, 1024 0.38; three filters a CU on more than four waves each (their
+// waves no longer divide over the SIMDs): 700 SEIR filters, N_x = 300, 256 threads 1.6 ms, 320
+// 1.9. Against 256 threads: 100 linear-Gaussian filters, N_x = 257, 0.66 -> 0.60 ms; 512 SEIR
 // filters with scores, N_x = 500, 1.94 -> 1.60; 200 age-structured filters, N_x = 700, 5.28 -> 4.34.
-static int pf_few_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
+static int pf_few_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters,
+                                int n_cu)
 {
-    const int per_cu = n_filters <= 256 ? 1 : 2, full = (nx + 63) / 64, items = day_items(model, nx);
+    const int per_cu = n_filters <= n_cu ? 1 : 2, full = (nx + 63) / 64, items = day_items(model, nx);
     const int most = items < 8 ? items : (full > 8 ? full : 8);
     const int start = most < 16 / per_cu ? most : 16 / per_cu;
     // not below half of it: two narrow filters a CU are no match for one on all its waves
@@ -1376,10 +1377,11 @@ static int pf_most_waves_block(int model, int prec, int nx, int T, int requested
 //    wide workgroups (600 linear-Gaussian filters, N_x = 1000, 200 days: three rounds of 1024
 //    threads 3.49 ms, one of 256 2.17; 2500, N_x = 512: 512 threads 1.05, 256 0.79).
 // Over 1955 launches per draw (the four models, SEIR and SIR in both precisions, SEIR and
-// linear-Gaussian with scores, 513 to 12288 filters, N_x = 40 to 4096) the size taken is 0.4% slower
+// linear-Gaussian with scores, 513 to 12288 filters on 256 CUs, N_x = 40 to 4096) the size taken is 0.4% slower
 // than the fastest of nine in the geometric mean, 3% at the 95th percentile and 16% at most; the
 // most resident waves alone 5%, 31% and 57%. Over 1225 pooled ones 1.6%, 12% and 32%; 6%, 31%, 54%.
-static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
+static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters,
+                                 int n_cu)
 {
     static const int sizes[] = {64, 128, 192, 256, 512, 1024};
     const int chunks = (nx + 63) / 64, items = day_items(model, nx), flows = items / chunks;
@@ -1391,7 +1393,7 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
         if (sc < 0) return 0.0;
         const size_t lds = pf_lds_bytes(model, prec, b, nx, T, sc);
         if (lds > PF_LDS_MAX) return 0.0;
-        const int per_cu = pf_resident(lds, w), round = 256 * per_cu;
+        const int per_cu = pf_resident(lds, w), round = n_cu * per_cu;
         const bool several = n_filters > round;
         if (w > chunks && several) return 0.0;
         const double mean = (double)chunks / w;
@@ -1402,7 +1404,7 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
             const double s = (groups * w + 3) / 4 / 4.0;
             return passes * (0.5 + 0.5 * s) + (several ? day * s : 0.0);
         };
-        const int rounds = n_filters / round, last = (n_filters - rounds * round + 255) / 256;
+        const int rounds = n_filters / round, last = (n_filters - rounds * round + n_cu - 1) / n_cu;
         return rounds * time(per_cu) + (last > 0 ? time(last) : 0.0);
     };
     int best = 0;
@@ -1419,12 +1421,22 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
     return best == 0 || (usual_time > 0.0 && best_time > 0.93 * usual_time) ? usual : best;
 }
 
-int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters)
+int pf_device_cus()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+        return n;
+    (void)hipGetLastError();  // without a device the call fails later, with its own error
+    return 256;
+}
+
+int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters, int n_cu)
 {
     if (n_filters > 0) {
-        const int b = n_filters <= 512
-                          ? pf_few_filters_block(model, prec, nx, T, requested_sched, score, n_filters)
-                          : pf_many_filters_block(model, prec, nx, T, requested_sched, score, n_filters);
+        const int b = n_filters <= 2 * n_cu
+                          ? pf_few_filters_block(model, prec, nx, T, requested_sched, score, n_filters, n_cu)
+                          : pf_many_filters_block(model, prec, nx, T, requested_sched, score, n_filters, n_cu);
         if (b > 0) return b;
     }
     // launches of runs of different sizes

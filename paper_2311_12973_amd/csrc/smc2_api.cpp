@@ -472,10 +472,11 @@ extern "C" int smc2_init(const smc2_config* cfg, int32_t n_runs, const smc2_run*
     const int want = cfg->schedule;
     const int pooled_variant = lgv ? PF_SCHED_SCORE_POOLED : PF_SCHED_POOLED;
     const int per_draw_variant = lgv ? PF_SCHED_SCORE : PF_SCHED_PER_DRAW;
+    const int n_cu = pf_device_cus();
     for (int r = 0; r < n_runs; ++r)
         blk[r] = cfg->block ? cfg->block
                             : pf_default_block(cfg->model, cfg->precision, runs[r].n_x, runs[r].T, want, lgv,
-                                               n_runs == 1 ? cfg->N : 0);
+                                               n_runs == 1 ? cfg->N : 0, n_cu);
     std::vector<int> run_order(n_runs);
     for (int r = 0; r < n_runs; ++r) run_order[r] = r;
     std::stable_sort(run_order.begin(), run_order.end(), [&](int a, int b) {
@@ -1101,7 +1102,8 @@ extern "C" int smc2_pmcmc_init(const smc2_config* cfg, int32_t chains, int32_t i
     if (!d_workspace || ws_bytes < L.total || ((uintptr_t)d_workspace & 255u))
         return g_thread_error = "workspace missing, too small or not 256-byte aligned", SMC2_E_ARG;
     const int block = cfg->block ? cfg->block
-                                 : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, cfg->schedule, false, chains);
+                                 : pf_default_block(cfg->model, cfg->precision, run->n_x, run->T, cfg->schedule, false,
+                                                    chains, pf_device_cus());
     const int sched = pf_pick_schedule(cfg->model, cfg->precision, block, run->n_x, run->T, cfg->schedule);
     if (sched < 0) return g_thread_error = "the pooled schedule cannot run this model, n_x and T", SMC2_E_ARG;
     const size_t lds = pf_lds_bytes(cfg->model, cfg->precision, block, run->n_x, run->T, sched);

@@ -31,10 +31,10 @@ def test_a_shape_is_accepted_whatever_the_number_of_filters(preset, prec, score,
         assert rc == (G.E_DEVICE if fits else G.E_ARG), (n, L.smc2_last_error(None))
 
 
-def _default_block(model, prec, nx, T, n_filters, schedule=G.SCHED_AUTO, score=False):
-    f = G.lib()._ZN4smc216pf_default_blockEiiiiibi
-    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_bool, ctypes.c_int]
-    return f(model, prec, nx, T, schedule, score, n_filters)
+def _default_block(model, prec, nx, T, n_filters, schedule=G.SCHED_AUTO, score=False, n_cu=256):
+    f = G.lib()._ZN4smc216pf_default_blockEiiiiibii
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_bool, ctypes.c_int, ctypes.c_int]
+    return f(model, prec, nx, T, schedule, score, n_filters, n_cu)
 
 
 @pytest.mark.parametrize("model,prec,score,n,nx,T,fastest", [
@@ -51,3 +51,14 @@ def _default_block(model, prec, nx, T, n_filters, schedule=G.SCHED_AUTO, score=F
 def test_many_filters_take_the_size_that_measured_fastest(model, prec, score, n, nx, T, fastest):
     """Shapes where the sizes' times lie far apart (10% to 60%): the fastest of those measured."""
     assert _default_block(model, prec, nx, T, n, score=score) == fastest
+
+
+@pytest.mark.parametrize("model,prec", [(G.SIR, G.PREC_FP64), (G.SEIR, G.PREC_FP32), (G.AGE_SEIR, G.PREC_FP32)])
+def test_the_size_follows_the_device_s_cus(model, prec):
+    """An eighth of the filters on a partition of an eighth of the CUs run on the same size; as many
+    as fill the whole card do not."""
+    for nx in (64, 100, 300, 700, 1000, 2000):
+        for per_cu in (0.25, 1, 2, 2.25, 4, 9, 33):
+            assert (_default_block(model, prec, nx, 60, int(32 * per_cu), n_cu=32) ==
+                    _default_block(model, prec, nx, 60, int(256 * per_cu)))
+    assert _default_block(G.SEIR, G.PREC_FP32, 1000, 60, 256, n_cu=32) < _default_block(G.SEIR, G.PREC_FP32, 1000, 60, 256)
