@@ -32,6 +32,26 @@ int smc2_philox_batch(int32_t n, const uint32_t* d_ctr, uint64_t seed, uint32_t*
 int smc2_binomial_batch(int32_t precision, int32_t count, const int32_t* d_n, const double* d_p, uint64_t seed,
                         uint32_t i, uint32_t k, uint32_t t, uint32_t b, int32_t* d_out, void* hip_stream);
 
+/* One scalar piece of the particle filter at `count` argument triples (d_a, d_b, d_c: double[count],
+ * rounded to `precision` where the filter holds them so), as the filter evaluates it (form 0) or as
+ * it is defined, by the library functions in FP64 and the general division and root (form 1). The two
+ * are equal to the last bit (a zero's sign aside). d_out: double[count], values of `precision`.
+ *   SMC2_TERM_LEAVE      1 - exp(-a): the probability of leaving a compartment at hazard a
+ *   SMC2_TERM_INVERSION  (1 - b)^a, a trials, 0 < b <= 1/2, a b < 10: the inversion's first term; c = 1:
+ *                        with the logarithm and the value at a = 1 computed once, c = 0: without
+ *   SMC2_TERM_NB         a log1p(c / b) + c log1p(b / c): the particle's part of minus the
+ *                        negative-binomial log-pmf of a cases at mean b, dispersion c
+ *   SMC2_TERM_CANDIDATE  the rejection sampler's candidate for a trials below 2^30 with probability b
+ *                        (b <= 1/2, a b >= 10) from the words u = c mod 2^32, v = floor(c / 2^32) 2^11:
+ *                        k when the squeeze accepts it, k + 1/2 when the final test decides, -1 outside
+ * Other arguments give values without meaning. */
+#define SMC2_TERM_LEAVE 0
+#define SMC2_TERM_INVERSION 1
+#define SMC2_TERM_NB 2
+#define SMC2_TERM_CANDIDATE 3
+int smc2_term_batch(int32_t precision, int32_t term, int32_t form, int32_t count, const double* d_a, const double* d_b,
+                    const double* d_c, double* d_out, void* hip_stream);
+
 /* Integer systematic resampling (Sec. IV-B, Eq. cdf and ncopies, Alg. 1) of n_sets
  * independent sets of n quantised weights (d_q: uint64[n_sets][n], each set with a
  * positive total below 2^47): d_anc[s][m] = min{ j : n C_j > m Q + U } with C the

@@ -25,6 +25,7 @@ PF_RS_SYSTEMATIC, PF_RS_MULTINOMIAL = 0, 1
 MLP_TRAIN_AUTO, MLP_TRAIN_PER_RUN, MLP_TRAIN_SPLIT = 0, 1, 2
 SCHED_AUTO, SCHED_PER_DRAW, SCHED_POOLED = 0, 1, 2
 LAUNCH_AUTO, LAUNCH_PERSISTENT, LAUNCH_PER_FILTER = 0, 1, 2
+TERM_LEAVE, TERM_INVERSION, TERM_NB, TERM_CANDIDATE = 0, 1, 2, 3
 DUMP = dict(phi=0, lp=1, ll=2, logw=3, phi_new=4, lp_new=5, ll_new=6, logw_pre=7, anc=8, mlp_out=9, logq=10,
             mlp_params=11, mlp_frame=12, mlp_state=13, mlp_grad=14, psteps=15, lkfit=16, theta_new=17, score=18,
             score_new=19)
@@ -125,6 +126,8 @@ def lib():
         L.smc2_binomial_batch.restype = c.c_int
         L.smc2_binomial_batch.argtypes = [c.c_int32, c.c_int32, vp, vp, c.c_uint64, c.c_uint32, c.c_uint32,
                                           c.c_uint32, c.c_uint32, vp, vp]
+        L.smc2_term_batch.restype = c.c_int
+        L.smc2_term_batch.argtypes = [c.c_int32, c.c_int32, c.c_int32, c.c_int32, vp, vp, vp, vp, vp]
         L.smc2_resample_batch.restype = c.c_int
         L.smc2_resample_batch.argtypes = [c.c_int32, c.c_int32, vp, vp, vp, vp, vp]
         L.smc2_pf_workspace_bytes.restype = c.c_size_t
@@ -378,6 +381,16 @@ def binomial_batch(precision, n, p, seed, i=0, k=1, t=1, b=0, device="cuda"):
     to, po = device_buffer(4 * cnt, device)
     _check(lib().smc2_binomial_batch(precision, cnt, pn, pp, int(seed), i, k, t, b, po, current_stream()))
     return from_device(to, po, np.int32, cnt)
+
+
+def term_batch(precision, term, a, b=0.0, c=0.0, form=0, device="cuda"):
+    """One scalar piece of the particle filter (TERM_*) at the broadcast arguments: as the filter
+    evaluates it (form 0) or by the functions that define it (form 1), as doubles."""
+    a, b, c = (np.ascontiguousarray(x, dtype=np.float64) for x in np.broadcast_arrays(a, b, c))
+    bufs = [to_device(x, device) for x in (a, b, c)]
+    to, po = device_buffer(8 * a.size, device)
+    _check(lib().smc2_term_batch(precision, term, form, a.size, *[x[1] for x in bufs], po, current_stream()))
+    return from_device(to, po, np.float64, a.size).reshape(a.shape)
 
 
 def resample_batch(q, x64, device="cuda"):

@@ -131,6 +131,18 @@ extern "C" int smc2_binomial_batch(int32_t precision, int32_t count, const int32
     return e == hipSuccess ? SMC2_OK : kfail(SMC2_E_DEVICE, hipGetErrorString(e));
 }
 
+extern "C" int smc2_term_batch(int32_t precision, int32_t term, int32_t form, int32_t count, const double* d_a,
+                               const double* d_b, const double* d_c, double* d_out, void* stream)
+{
+    if (precision != SMC2_PREC_FP32 && precision != SMC2_PREC_FP64) return kfail(SMC2_E_ARG, "bad precision");
+    if (term < SMC2_TERM_LEAVE || term > SMC2_TERM_CANDIDATE) return kfail(SMC2_E_ARG, "unknown term");
+    if (form < 0 || form > 1) return kfail(SMC2_E_ARG, "form must be 0 or 1");
+    if (count < 0 || (count > 0 && (!d_a || !d_b || !d_c || !d_out))) return kfail(SMC2_E_ARG, "bad term arguments");
+    if (count == 0) return SMC2_OK;
+    const hipError_t e = launch_pf_terms(precision, term, form, count, d_a, d_b, d_c, d_out, (hipStream_t)stream);
+    return e == hipSuccess ? SMC2_OK : kfail(SMC2_E_DEVICE, hipGetErrorString(e));
+}
+
 extern "C" int smc2_resample_batch(int32_t n_sets, int32_t n, const uint64_t* d_q, const uint64_t* d_x64,
                                    int32_t* d_anc, int32_t* d_trigger, void* stream)
 {

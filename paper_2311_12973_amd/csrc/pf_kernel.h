@@ -78,6 +78,10 @@ int pf_default_block(int model, int prec, int nx, int T, int requested_sched, bo
 // CUs of the current device (a partition has fewer than the card's 256).
 int pf_device_cus();
 bool pf_supported(int model, int obs);
+// One scalar piece of the filter (SMC2_TERM_*), for tests: form 0 as the filter evaluates it, form 1
+// by the functions that define it.
+hipError_t launch_pf_terms(int prec, int term, int form, int count, const double* a, const double* b, const double* c,
+                           double* out, hipStream_t s);
 // Raise the dynamic-LDS limit of the kernel when a launch needs more than 64 KiB.
 hipError_t pf_prepare(int prec, int model, int obs, int sched, size_t lds);
 hipError_t launch_pf(int prec, int model, int obs, int sched, int block, size_t lds, const PFArgs& a,

@@ -1274,7 +1274,73 @@ __global__ void __launch_bounds__(1024) k_pf(PFArgs a)
     }
 }
 
+// ---------------------------------------------------------------- single terms
+// The definition of the rejection sampler's candidate: general root and division, floor and clamp.
+template <typename real>
+__device__ int candidate_general(int32_t n, real p, uint32_t wu, uint32_t wv, int32_t& k)
+{
+    const double npq = (double)(((real)n * p) * ((real)1 - p));
+    const real spq = (real)sqrt(npq);  // the FP64 root rounded to FP32 is the correctly rounded one
+    const real bb = (real)1.15 + (real)2.53 * spq;
+    const real vr = (real)0.92 - (real)4.2 / bb, aa = ((real)-0.0873 + (real)0.0248 * bb) + (real)0.01 * p;
+    const double cc = (double)n * (double)p + 0.5;
+    const real u = (real)u24(wu) - (real)0.5, v = (real)u24(wv), us = (real)0.5 - (real)fabs((double)u);
+    const real t = ((((real)2 * aa) / us) + bb) * u + (real)(cc - floor(cc));
+    const double kd = floor(cc) + floor((double)t);
+    if (kd < 0.0 || kd > (double)n) return BTRS_OUT;
+    k = (int32_t)kd;
+    return us >= (real)0.07 && v <= vr ? BTRS_ACCEPT : BTRS_FINAL;
+}
+
+template <typename real>
+__global__ void __launch_bounds__(256) k_terms(int term, int form, int count, const double* a, const double* b,
+                                               const double* c, double* out)
+{
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i >= count) return;
+    const bool lib = form == 1;
+    const double x = a[i], z = b[i], y = c[i];
+    double v = 0.0;
+    if (term == 0) {
+        v = (double)(lib ? (real)-expm1(-(double)(real)x) : leave_prob<real>((real)x));
+    } else if (term == 1) {
+        const real p = (real)z;
+        const double l1p = y != 0.0 ? log1p(-(double)p) : NAN;
+        if constexpr (sizeof(real) == 4) {
+            v = lib ? inversion_first<float>((int32_t)x, p, l1p)
+                    : inversion_first_fast((int32_t)x, p, l1p, (float)exp(l1p));
+        } else {
+            v = inversion_first<double>((int32_t)x, p, l1p);
+        }
+    } else if (term == 2) {
+        MConst<real> mc;
+        mc.r = y;
+        mc.r_ok = y >= 0x1p-30 && y <= 0x1p30;
+        mc.lr1 = -0x1.62e42fefa39efp-2 - log(y);
+        const int32_t cases[1] = {(int32_t)x}, mean[1] = {(int32_t)z};
+        v = -(double)(lib ? (real)obs_part<OBS_NB_INC>(cases[0], mean[0], y) : nb_obs<real, 1>(mc, cases, mean));
+    } else {
+        const uint64_t w = (uint64_t)y;
+        const uint32_t wu = (uint32_t)w, wv = (uint32_t)(w >> 32) << 11;
+        const int32_t n = (int32_t)x;
+        const real p = (real)z;
+        int32_t k = 0;
+        const int t = lib ? candidate_general<real>(n, p, wu, wv, k) : btrs_try<real>(btrs_setup<real>(n, p), n, wu, wv, k);
+        v = t == BTRS_OUT ? -1.0 : (double)k + (t == BTRS_FINAL ? 0.5 : 0.0);
+    }
+    out[i] = v;
+}
+
 // ---------------------------------------------------------------- host side
+
+hipError_t launch_pf_terms(int prec, int term, int form, int count, const double* a, const double* b, const double* c,
+                           double* out, hipStream_t s)
+{
+    const dim3 g((unsigned)((count + 255) / 256)), blk(256);
+    if (prec == 0) hipLaunchKernelGGL(k_terms<float>, g, blk, 0, s, term, form, count, a, b, c, out);
+    else hipLaunchKernelGGL(k_terms<double>, g, blk, 0, s, term, form, count, a, b, c, out);
+    return hipGetLastError();
+}
 
 int pf_score_dims(int model)
 {
