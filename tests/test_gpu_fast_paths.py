@@ -177,3 +177,47 @@ def test_flows_of_one_particle_on_several_waves(preset, nx, block):
     a, sa = G.pf_score(w, theta, y, nx, 9, 2, block=block)
     b, sb = G.pf_score(w, theta, y, nx, 9, 2, block=64)
     assert np.array_equal(a, b) and np.array_equal(sa, sb)
+
+
+def _under_way(preset, T):
+    """A small SEIR epidemic whose filters live to the last day: nobody is exposed at the start, so
+    the first day reports no case; about n p = 10 to 20 from the second day on."""
+    w = dict(W.preset(preset), n_pop=4000.0, T=T)
+    truth = np.array(w["truth"])
+    truth[1:4] = 0.12, 0.15, 0.1 if preset == "age_seir" else 0.025
+    y = np.full((T, 4 if preset == "age_seir" else 1), 12, dtype=np.int32)
+    y[0] = 0
+    theta = np.tile(truth, (4, 1)) * np.exp(np.random.default_rng(T).normal(0, 0.05, (4, w["D"])))
+    return w, theta, y
+
+
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+@pytest.mark.parametrize("preset,nx,block", [
+    ("seir", 63, 64), ("seir", 65, 64), ("seir", 640, 64), ("seir", 641, 64), ("seir", 200, 128), ("seir", 130, 192),
+    ("seir", 130, 256), ("seir", 130, 448), ("seir", 130, 1024), ("age_seir", 63, 64), ("age_seir", 65, 64),
+    ("age_seir", 200, 64), ("age_seir", 200, 256), ("age_seir", 300, 1024)])
+def test_open_draws_through_an_epidemic(preset, nx, block, prec):
+    """Draws out of every compartment left open and settled, day after day: in place, over as many
+    passes as a mask holds and one more, spread over waves, and the age groups' (an open E whose I
+    is open too)."""
+    w, theta, y = _under_way(preset, 7)
+    _same_filters(w, theta, y, nx, prec=prec, schedule=G.SCHED_PER_DRAW, block=block)
+    ll = G.pf_loglik(w, theta, y, nx, seed=9, k=2, precision=prec, schedule=G.SCHED_PER_DRAW, block=block)
+    assert np.isfinite(ll).all()  # every day was compared
+
+
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+@pytest.mark.parametrize("preset", ["seir", "age_seir"])
+def test_increments_of_every_day(preset, prec):
+    """Day by day the likelihood increments of filters that live. The counts and the weights'
+    bits are the reference's, so what may differ are logarithms and log-gammas of terms below 100:
+    100 roundings of 2^-53 each, 1.1e-12, ten times that allowed. One FP32 weight with a wrong
+    last bit (2^-24 of a log-weight of 2 or more, among 100 particles) moves an increment by 1e-9."""
+    w, theta, y = _under_way(preset, 12)
+    _, inc, rs, _ = G.pf_trace_state(w, theta, y, 100, seed=4, k=1, precision=prec)
+    cfg = O.config_from_workload(w, prec=prec)
+    for i, th in enumerate(theta):
+        _, ref, rs_ref, _ = O.pf_trace_state(cfg, th, y, 100, 4, i, 1)
+        assert np.isfinite(ref).all() and np.array_equal(rs[i], rs_ref)
+        print(preset, prec, i, np.abs(inc[i] - ref).max(), flush=True)
+        assert np.abs(inc[i] - ref).max() <= 1.1e-11

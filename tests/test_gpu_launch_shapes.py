@@ -71,3 +71,27 @@ def test_autotuner_times_the_default_size_too():
     assert np.array_equal(a.records(), b.records())
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("block", [64, 128, 192, 448, 1024])
+@pytest.mark.parametrize("nx", [60, 130, 700])
+@pytest.mark.parametrize("preset", ["sir_fp64", "seir", "seir_learned"])
+@pytest.mark.parametrize("prec", [G.PREC_FP32, G.PREC_FP64])
+def test_scores_do_not_depend_on_where_the_flows_are_drawn(prec, preset, nx, block):
+    """Scores with flows drawn in place, in several passes of a wave and spread over waves, where
+    the probability of leaving S is kept beside the flows or, FP64 SEIR, computed again: the bits of
+    the pooled launch, which computes it from the counts."""
+    w = dict(W.preset(preset), n_pop=4000.0, T=6)
+    truth = np.array(w["truth"])
+    if preset == "sir_fp64":
+        w["fixed"], truth[1] = [120], 0.12
+    else:
+        truth[1:4] = 0.12, 0.15, 0.025
+    y = np.full((6, 1), 12, dtype=np.int32)
+    y[0] = 0 if preset != "sir_fp64" else 12  # SEIR: nobody is exposed yet, and no case on the first day
+    theta = np.tile(truth, (4, 1)) * np.exp(np.random.default_rng(nx).normal(0, 0.05, (4, w["D"])))
+    print("scores", prec, preset, nx, block, flush=True)
+    a, sa = G.pf_score(w, theta, y, nx, 9, 2, precision=prec, schedule=G.SCHED_PER_DRAW, block=block)
+    b, sb = G.pf_score(w, theta, y, nx, 9, 2, precision=prec, schedule=G.SCHED_POOLED, block=64)
+    assert np.isfinite(b).all() and (sb[:, :2] != 0).all()
+    assert np.array_equal(a, b) and np.array_equal(sa, sb)
