@@ -10,12 +10,17 @@ namespace smc2 {
 struct RedLds {
     double max_d[16];
     float max_f[16];
-    double sum_d[16];
     uint64_t sum_a[16];
     uint64_t sum_b[16];
     uint64_t scan[16];
-    double chunk[64];  // sums of 64 particles each: those of N_x <= 4096, none for a row's end beyond them
+    // sums of 64 particles each: 64 for N_x <= 4096, and up to 15, all zero, for the rows' ends where a
+    // workgroup size rounds N_x up beyond that (960 to 4800)
+    double chunk[80];
 };
+static_assert(4096 + 1024 <= 80 * 64, "chunk sums of N_x rounded up to any workgroup size");
+// block_sum3's slots, the last 16 of the chunk sums. A filter that keeps a value there beside its
+// chunk sums has rows of at most 64 chunks (score launches: their columns fill the LDS before).
+__device__ __forceinline__ double* red_sum_slot(RedLds* r) { return r->chunk + 64; }
 
 template <typename real> __device__ __forceinline__ real* red_max_slot(RedLds* r);
 template <> __device__ __forceinline__ float* red_max_slot<float>(RedLds* r) { return r->max_f; }
@@ -69,17 +74,17 @@ __device__ __forceinline__ void block_sum3(double& s, uint64_t& a, uint64_t& b, 
     a = wave_sum(a);
     b = wave_sum(b);
     if (lane_id() == 0) {
-        red->sum_d[wave_id()] = s;
+        red_sum_slot(red)[wave_id()] = s;
         red->sum_a[wave_id()] = a;
         red->sum_b[wave_id()] = b;
     }
     __syncthreads();
     const int nw = (int)(blockDim.x >> 6);
-    s = red->sum_d[0];
+    s = red_sum_slot(red)[0];
     a = red->sum_a[0];
     b = red->sum_b[0];
     for (int w = 1; w < nw; ++w) {
-        s += red->sum_d[w];
+        s += red_sum_slot(red)[w];
         a += red->sum_a[w];
         b += red->sum_b[w];
     }

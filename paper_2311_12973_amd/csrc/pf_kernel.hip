@@ -974,7 +974,6 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
     const int T = run.T, nx = run.nx;
     const uint32_t kit = (uint32_t)uniform_i32(a.k_dev ? *a.k_dev : (int32_t)a.k_const);
     const int cap = ((nx + nthr - 1) / nthr) * nthr;
-    const int n_chunks = (nx + 63) >> 6;  // of 64 particles, at most 64
 
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int wg_next;  // next draw item of the day (pooled schedule)
@@ -1129,8 +1128,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
         // 2. normalise by the maximum; FP64 sum and quantised weights. At step s wave w
         //    holds the 64 consecutive particles of chunk s W + w; each chunk is summed by
         //    a wave butterfly and the chunk sums in chunk order, so the sum (and the
-        //    likelihood) does not depend on the workgroup size. Chunks beyond N_x (a workgroup
-        //    size that rounds N_x up by more than 63) hold no weight and have no slot.
+        //    likelihood) does not depend on the workgroup size. Chunks beyond N_x sum to zero.
         uint64_t q1 = 0, q2 = 0;
         const int nwv = nthr >> 6;
         for (int j = tid, step = 0; j < cap; j += nthr, ++step) {
@@ -1150,8 +1148,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
                 lw[j] = av - m;
             }
             const double cs = wave_sum(w);
-            const int ch = step * nwv + wave_id();
-            if (lane_id() == 0 && ch < n_chunks) red->chunk[ch] = cs;
+            if (lane_id() == 0) red->chunk[step * nwv + wave_id()] = cs;
         }
         block_sum_u64(q1, q2, red);
         // 3. resample when ESS < N_x / 2 (never after the last observation)
@@ -1160,7 +1157,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
         // chain of some 200 instructions that the other waves need not repeat or wait for
         if (first_wave()) {
             double sl = 0.0;
-            for (int c = 0; c < n_chunks; ++c) sl += red->chunk[c];
+            for (int c = 0; c < (cap >> 6); ++c) sl += red->chunk[c];
             sl_last = sl;
             const double lsl = log(sl);
             const double inc = (((double)m + lsl) - log_prev) + cst[t - 1];
@@ -1216,22 +1213,21 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
         // summed per 64-particle chunk and the chunks in order, like the weight sum. The
         // chunk slots still hold the last day's weight sums, which every thread has read
         // only once all have passed this barrier.
-        if (first_wave()) red->sum_d[0] = ll;
+        if (first_wave()) red_sum_slot(red)[0] = ll;
         __syncthreads();
         const double* wT = reinterpret_cast<const double*>(C);
         const int nwv = nthr >> 6;
-        const bool alive = uniform_bool(red->sum_d[0] != -INFINITY);
+        const bool alive = uniform_bool(red_sum_slot(red)[0] != -INFINITY);
         for (int d = 0; d < a.D; ++d) {
             double num = 0.0;
             if (alive && d < NS) {
                 for (int j = tid, step = 0; j < cap; j += nthr, ++step) {
                     const double v = j < nx ? wT[j] * lds_f64(sw + 2 * d * cap, cap, j) : 0.0;
                     const double cs = wave_sum(v);
-                    const int ch = step * nwv + wave_id();
-                    if (lane_id() == 0 && ch < n_chunks) red->chunk[ch] = cs;
+                    if (lane_id() == 0) red->chunk[step * nwv + wave_id()] = cs;
                 }
                 __syncthreads();
-                for (int c = 0; c < n_chunks; ++c) num += red->chunk[c];
+                for (int c = 0; c < (cap >> 6); ++c) num += red->chunk[c];
                 __syncthreads();  // the chunk slots are reused by the next coordinate
             }
             if (tid == 0) a.score[(size_t)g * a.D + d] = alive ? num / sl_last : 0.0;
