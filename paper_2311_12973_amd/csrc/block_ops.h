@@ -26,26 +26,25 @@ template <typename real> __device__ __forceinline__ real* red_max_slot(RedLds* r
 template <> __device__ __forceinline__ float* red_max_slot<float>(RedLds* r) { return r->max_f; }
 template <> __device__ __forceinline__ double* red_max_slot<double>(RedLds* r) { return r->max_d; }
 
-// The reductions and scans below join the waves' results in a second step; a workgroup of one wave
-// is done after the first (4483 linear-Gaussian filters, N_x = 32, 150 days: 0.916 ms with the second
-// step, 0.873 without).
+// ONE: the workgroup is a single wave, and the second step of the reductions and scans, which joins
+// the waves' results, falls away (4483 linear-Gaussian filters, N_x = 32, 150 days: 0.925 -> 0.875 ms).
 
 // Maximum over the block (exact, order-free).
-template <typename real> __device__ __forceinline__ real block_max(real v, RedLds* red)
+template <typename real, bool ONE = false> __device__ __forceinline__ real block_max(real v, RedLds* red)
 {
     real* slot = red_max_slot<real>(red);
     v = wave_max(v);
     if (lane_id() == 0) slot[wave_id()] = v;
     __syncthreads();
     const int nw = (int)(blockDim.x >> 6);
-    if (nw == 1) return uniform_real<real>(v);
+    if constexpr (ONE) return uniform_real<real>(v);
     // every wave reads the slots into its first lanes and reduces them there
     const real m = slot[lane_id() < nw ? lane_id() : 0];
     return uniform_real<real>(row_reduce(m, [](real x, real u) { return u > x ? u : x; }));
 }
 
 // Sums of two u64 values over the block, as scalars.
-__device__ __forceinline__ void block_sum_u64(uint64_t& a, uint64_t& b, RedLds* red)
+template <bool ONE = false> __device__ __forceinline__ void block_sum_u64(uint64_t& a, uint64_t& b, RedLds* red)
 {
     a = wave_sum(a);
     b = wave_sum(b);
@@ -55,7 +54,7 @@ __device__ __forceinline__ void block_sum_u64(uint64_t& a, uint64_t& b, RedLds* 
     }
     __syncthreads();
     const int nw = (int)(blockDim.x >> 6), l = lane_id() < nw ? lane_id() : 0;
-    if (nw == 1) {
+    if constexpr (ONE) {
         a = uniform_u64(a);
         b = uniform_u64(b);
         return;
@@ -100,17 +99,17 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l)
 
 // Exclusive scan over the block (thread order); returns the exclusive prefix and
 // the block total.
-__device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t& total, RedLds* red)
+template <bool ONE = false> __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t& total, RedLds* red)
 {
     const uint64_t incl = wave_incl_scan(v);
     if (lane_id() == 63) red->scan[wave_id()] = incl;
     __syncthreads();
-    // every wave scans the slots in its first row: the total, and its own offset
-    const int nw = (int)(blockDim.x >> 6), me = uniform_i32(wave_id());
-    if (nw == 1) {
+    if constexpr (ONE) {
         total = lane_u64(incl, 63);
         return incl - v;
     }
+    // every wave scans the slots in its first row: the total, and its own offset
+    const int nw = (int)(blockDim.x >> 6), me = uniform_i32(wave_id());
     const uint64_t slot = red->scan[lane_id() < nw ? lane_id() : 0];
     const uint64_t own = lane_id() < nw ? slot : 0ull;
     const uint64_t to = row_incl_scan(own);
@@ -132,7 +131,7 @@ __device__ __forceinline__ bool ess_below_half(uint64_t s1, uint64_t s2, int n)
 // so the result is the scan in index order whatever the block size. The caller
 // must have made C visible to all threads (a barrier) before the call; C is visible
 // to all threads on return.
-__device__ __forceinline__ uint64_t block_scan_lds(uint64_t* C, int n, RedLds* red)
+template <bool ONE = false> __device__ __forceinline__ uint64_t block_scan_lds(uint64_t* C, int n, RedLds* red)
 {
     const int nthr = (int)blockDim.x, tid = (int)threadIdx.x;
     const int chunk = (n + nthr - 1) / nthr;
@@ -141,7 +140,7 @@ __device__ __forceinline__ uint64_t block_scan_lds(uint64_t* C, int n, RedLds* r
     uint64_t acc = 0;
     for (int e = lo; e < hi; ++e) acc += C[e];
     uint64_t total;
-    uint64_t off = block_excl_scan(acc, total, red);
+    uint64_t off = block_excl_scan<ONE>(acc, total, red);
     for (int e = lo; e < hi; ++e) {
         off += C[e];
         C[e] = off;

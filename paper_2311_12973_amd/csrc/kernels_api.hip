@@ -290,7 +290,7 @@ static int pf_run(const smc2_config* cfg, int32_t n_theta, const double* d_theta
     a.multinomial = cfg->pf_resampling;
     a.n_pop = cfg->n_pop;
     for (int i = 0; i < SMC2_NFIXED; ++i) a.fx[i] = i < cfg->n_fixed ? cfg->fixed[i] : 0.0;
-    if (e == hipSuccess) e = pf_prepare(cfg->precision, cfg->model, cfg->obs, sched, lds);
+    if (e == hipSuccess) e = pf_prepare(cfg->precision, cfg->model, cfg->obs, sched, block, lds);
     // wave priorities when every filter is resident at once (they even out its tail)
     int per_cu = 0;
     if (e == hipSuccess) e = pf_occupancy(cfg->precision, cfg->model, cfg->obs, sched, block, lds, &per_cu);

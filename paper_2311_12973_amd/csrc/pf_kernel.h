@@ -83,7 +83,7 @@ bool pf_supported(int model, int obs);
 hipError_t launch_pf_terms(int prec, int term, int form, int count, const double* a, const double* b, const double* c,
                            double* out, hipStream_t s);
 // Raise the dynamic-LDS limit of the kernel when a launch needs more than 64 KiB.
-hipError_t pf_prepare(int prec, int model, int obs, int sched, size_t lds);
+hipError_t pf_prepare(int prec, int model, int obs, int sched, int block, size_t lds);
 hipError_t launch_pf(int prec, int model, int obs, int sched, int block, size_t lds, const PFArgs& a,
                      hipStream_t s, int grid = 0);
 // Workgroups of this configuration resident per CU (for sizing a persistent grid).

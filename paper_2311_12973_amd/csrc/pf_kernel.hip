@@ -941,7 +941,7 @@ __device__ __forceinline__ void wave_priority(float r)
     else __builtin_amdgcn_s_setprio(0);
 }
 
-template <typename real, int MODEL, int OBS, int SCHED>
+template <typename real, int MODEL, int OBS, int SCHED, bool ONE>
 __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a, int item)
 {
     constexpr int NC = ModelShape<MODEL>::NC;
@@ -1113,7 +1113,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
                 for (int c = 0; c < NC; ++c)
                     a.trace_state[(((size_t)g * T + (t - 1)) * NC + c) * nx + j] = st[c * cap + j];
         }
-        const real m = block_max<real>(amax, red);
+        const real m = block_max<real, ONE>(amax, red);
         if (m == (real)-INFINITY) {
             ll = -INFINITY;
             days = t;
@@ -1150,7 +1150,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             const double cs = wave_sum(w);
             if (lane_id() == 0) red->chunk[step * nwv + wave_id()] = cs;
         }
-        block_sum_u64(q1, q2, red);
+        block_sum_u64<ONE>(q1, q2, red);
         // 3. resample when ESS < N_x / 2 (never after the last observation)
         const bool rs = uniform_bool(t < T && (a.pf_always || ess_below_half(q1, q2, nx)));
         // the first wave alone keeps the likelihood: the ordered sum and the logarithm are a
@@ -1169,7 +1169,7 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
             }
         }
         if (rs) {
-            const uint64_t Q = block_scan_lds(C, nx, red);
+            const uint64_t Q = block_scan_lds<ONE>(C, nx, red);
             if (a.multinomial) {
                 multinomial_ancestors(C, nx, Q, filt, kt, run.k0, run.k1, anc);
             } else {
@@ -1243,12 +1243,14 @@ __device__ __attribute__((always_inline)) inline void pf_filter(const PFArgs& a,
 // Up to 1024 threads (16 waves) per workgroup, which caps the kernel at 128 VGPRs, i.e.
 // 4 waves per SIMD: occupancy hides the latency of the FP64 transcendental sequences
 // better than a larger register budget. Filters with a large LDS footprint run one
-// wide workgroup per CU; small ones run several 256-thread workgroups.
-template <typename real, int MODEL, int OBS, int SCHED>
+// wide workgroup per CU; small ones run several 256-thread workgroups. ONE: a kernel for workgroups of
+// one wave, whose reductions have no second step; for the linear-Gaussian model, whose days are
+// short enough to show it (as a branch in the common kernel it cost workgroups of more waves 0.7%).
+template <typename real, int MODEL, int OBS, int SCHED, bool ONE>
 __global__ void __launch_bounds__(1024) k_pf(PFArgs a)
 {
     if (!a.queue) {
-        if ((int)blockIdx.x < a.n_items) pf_filter<real, MODEL, OBS, SCHED>(a, (int)blockIdx.x);
+        if ((int)blockIdx.x < a.n_items) pf_filter<real, MODEL, OBS, SCHED, ONE>(a, (int)blockIdx.x);
         return;
     }
     // No branch on the thread index may sit at the top or the bottom of this loop: with
@@ -1266,7 +1268,7 @@ __global__ void __launch_bounds__(1024) k_pf(PFArgs a)
         const int item = uniform_i32(next_item);  // scalar: the loop exit is uniform
         __syncthreads();  // every thread has read the item before it is replaced
         if (item >= a.n_items) break;
-        pf_filter<real, MODEL, OBS, SCHED>(a, item);
+        pf_filter<real, MODEL, OBS, SCHED, ONE>(a, item);
     }
 }
 
@@ -1541,13 +1543,16 @@ template <typename real, int MODEL, int OBS, int SCHED>
 static hipError_t launch_one(int block, size_t lds, const PFArgs& a, hipStream_t s, int grid)
 {
     const unsigned g = (unsigned)(a.queue ? grid : a.n_items);
-    hipLaunchKernelGGL((k_pf<real, MODEL, OBS, SCHED>), dim3(g), dim3((unsigned)block), lds, s, a);
+    if (MODEL == MODEL_LG && block == 64)
+        hipLaunchKernelGGL((k_pf<real, MODEL, OBS, SCHED, MODEL == MODEL_LG>), dim3(g), dim3(64u), lds, s, a);
+    else
+        hipLaunchKernelGGL((k_pf<real, MODEL, OBS, SCHED, false>), dim3(g), dim3((unsigned)block), lds, s, a);
     return hipGetLastError();
 }
 
-template <typename real, int MODEL, int OBS, int SCHED> static const void* kernel_ptr()
+template <typename real, int MODEL, int OBS, int SCHED, bool ONE = false> static const void* kernel_ptr()
 {
-    return reinterpret_cast<const void*>(&k_pf<real, MODEL, OBS, SCHED>);
+    return reinterpret_cast<const void*>(&k_pf<real, MODEL, OBS, SCHED, ONE>);
 }
 
 template <typename real, int SCHED>
@@ -1567,7 +1572,7 @@ static hipError_t launch_model(int model, int obs, int block, size_t lds, const 
     return hipErrorInvalidValue;
 }
 
-template <typename real, int SCHED> static const void* kernel_of(int model, int obs)
+template <typename real, int SCHED> static const void* kernel_of(int model, int obs, int block)
 {
     if (model == MODEL_SIR && obs == OBS_POIS_PREV) return kernel_ptr<real, MODEL_SIR, OBS_POIS_PREV, SCHED>();
     if (model == MODEL_SIR && obs == OBS_POIS_INC) return kernel_ptr<real, MODEL_SIR, OBS_POIS_INC, SCHED>();
@@ -1575,7 +1580,9 @@ template <typename real, int SCHED> static const void* kernel_of(int model, int 
     if (model == MODEL_AGE && obs == OBS_NB_INC && SCHED == PF_SCHED_PER_DRAW)
         return kernel_ptr<real, MODEL_AGE, OBS_NB_INC, PF_SCHED_PER_DRAW>();
     if constexpr (std::is_same<real, double>::value && (SCHED == PF_SCHED_PER_DRAW || SCHED == PF_SCHED_SCORE))
-        if (model == MODEL_LG && obs == OBS_GAUSS) return kernel_ptr<double, MODEL_LG, OBS_GAUSS, SCHED>();
+        if (model == MODEL_LG && obs == OBS_GAUSS)
+            return block == 64 ? kernel_ptr<double, MODEL_LG, OBS_GAUSS, SCHED, true>()
+                               : kernel_ptr<double, MODEL_LG, OBS_GAUSS, SCHED>();
     return nullptr;
 }
 
@@ -1586,21 +1593,24 @@ bool pf_supported(int model, int obs)
            (model == MODEL_LG && obs == OBS_GAUSS);
 }
 
-static const void* kernel_for(int prec, int model, int obs, int sched)
+static const void* kernel_for(int prec, int model, int obs, int sched, int block)
 {
     if (sched == PF_SCHED_SCORE_POOLED)
-        return prec == 0 ? kernel_of<float, PF_SCHED_SCORE_POOLED>(model, obs)
-                         : kernel_of<double, PF_SCHED_SCORE_POOLED>(model, obs);
+        return prec == 0 ? kernel_of<float, PF_SCHED_SCORE_POOLED>(model, obs, block)
+                         : kernel_of<double, PF_SCHED_SCORE_POOLED>(model, obs, block);
     if (sched == PF_SCHED_POOLED)
-        return prec == 0 ? kernel_of<float, PF_SCHED_POOLED>(model, obs) : kernel_of<double, PF_SCHED_POOLED>(model, obs);
+        return prec == 0 ? kernel_of<float, PF_SCHED_POOLED>(model, obs, block)
+                         : kernel_of<double, PF_SCHED_POOLED>(model, obs, block);
     if (sched == PF_SCHED_SCORE)
-        return prec == 0 ? kernel_of<float, PF_SCHED_SCORE>(model, obs) : kernel_of<double, PF_SCHED_SCORE>(model, obs);
-    return prec == 0 ? kernel_of<float, PF_SCHED_PER_DRAW>(model, obs) : kernel_of<double, PF_SCHED_PER_DRAW>(model, obs);
+        return prec == 0 ? kernel_of<float, PF_SCHED_SCORE>(model, obs, block)
+                         : kernel_of<double, PF_SCHED_SCORE>(model, obs, block);
+    return prec == 0 ? kernel_of<float, PF_SCHED_PER_DRAW>(model, obs, block)
+                     : kernel_of<double, PF_SCHED_PER_DRAW>(model, obs, block);
 }
 
-hipError_t pf_prepare(int prec, int model, int obs, int sched, size_t lds)
+hipError_t pf_prepare(int prec, int model, int obs, int sched, int block, size_t lds)
 {
-    const void* f = kernel_for(prec, model, obs, sched);
+    const void* f = kernel_for(prec, model, obs, sched, block);
     if (!f) return hipErrorInvalidValue;
     if (lds <= 65536) return hipSuccess;
     // the attribute belongs to the kernel on the current device, shared by every launch
@@ -1643,7 +1653,7 @@ hipError_t launch_pf(int prec, int model, int obs, int sched, int block, size_t 
 
 hipError_t pf_occupancy(int prec, int model, int obs, int sched, int block, size_t lds, int* per_cu)
 {
-    const void* f = kernel_for(prec, model, obs, sched);
+    const void* f = kernel_for(prec, model, obs, sched, block);
     if (!f) return hipErrorInvalidValue;
     int n = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, block, lds);

@@ -355,7 +355,7 @@ static hipError_t autotune(smc2_ctx* c)
                                        ? gr.lds
                                        : pf_lds_bytes(cfg.model, cfg.precision, b, gr.max_nx, gr.max_T, sc);
                 if (lds > PF_LDS_MAX) continue;
-                e = pf_prepare(cfg.precision, cfg.model, cfg.obs, sc, lds);
+                e = pf_prepare(cfg.precision, cfg.model, cfg.obs, sc, b, lds);
                 for (int pers = 0; pers <= 1 && e == hipSuccess; ++pers) {
                     PFGroup cand = gr;
                     cand.block = b;
@@ -407,7 +407,7 @@ static hipError_t autotune(smc2_ctx* c)
                                                        c->runs[r].T, gr.sched));
             }
             if (gr.lds > PF_LDS_MAX) return hipErrorInvalidValue;
-            e = pf_prepare(cfg.precision, cfg.model, cfg.obs, gr.sched, gr.lds);
+            e = pf_prepare(cfg.precision, cfg.model, cfg.obs, gr.sched, gr.block, gr.lds);
         }
     }
     if (t0) (void)hipEventDestroy(t0);
@@ -519,7 +519,7 @@ extern "C" int smc2_init(const smc2_config* cfg, int32_t n_runs, const smc2_run*
             delete c;
             return g_thread_error = "particle filter does not fit in LDS (n_x or T too large)", SMC2_E_ARG;
         }
-        const hipError_t e = pf_prepare(cfg->precision, cfg->model, cfg->obs, gr.sched, gr.lds);
+        const hipError_t e = pf_prepare(cfg->precision, cfg->model, cfg->obs, gr.sched, gr.block, gr.lds);
         if (e != hipSuccess) {
             const int rc = c->device_fail(e, "pf_prepare");
             g_thread_error = c->err;
@@ -1178,7 +1178,7 @@ extern "C" int smc2_pmcmc_init(const smc2_config* cfg, int32_t chains, int32_t i
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host copies above are released below
     // wave priorities when every chain's filter is resident at once
     int per_cu = 0, n_cu = 0, dev = 0;
-    if (e == hipSuccess) e = pf_prepare(cfg->precision, cfg->model, cfg->obs, sched, lds);
+    if (e == hipSuccess) e = pf_prepare(cfg->precision, cfg->model, cfg->obs, sched, block, lds);
     if (e == hipSuccess) e = pf_occupancy(cfg->precision, cfg->model, cfg->obs, sched, block, lds, &per_cu);
     if (e == hipSuccess) e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
