@@ -1429,8 +1429,9 @@ static int pf_most_waves_block(int model, int prec, int nx, int T, int requested
 }
 
 // Larger launches: the workgroup size of the least estimated time, in units of a pass over
-// a workgroup's particles with all 16 wave slots of a CU taken, where that saves 7% against the
-// size of the most resident waves; else that size. What enters the estimate:
+// a workgroup's particles with all 16 wave slots of a CU taken, where that saves 5% against the
+// size of the most resident waves (7% for the linear-Gaussian model, whose passes are so short that
+// the estimate is further off); else that size. What enters the estimate:
 //  - a pass with s of a SIMD's four wave slots taken takes 0.5 + 0.5 s / 4;
 //  - a wave with a pass more than the average holds up its workgroup for a quarter of the
 //    difference (the other workgroups of the CU fill in the rest); spread draws for all of it,
@@ -1482,7 +1483,7 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
     }
     const int usual = pf_most_waves_block(model, prec, nx, T, requested_sched, score);
     const double usual_time = usual > 0 ? estimate(usual) : 0.0;
-    return best == 0 || (usual_time > 0.0 && best_time > 0.93 * usual_time) ? usual : best;
+    return best == 0 || (usual_time > 0.0 && best_time > (model == MODEL_LG ? 0.93 : 0.95) * usual_time) ? usual : best;
 }
 
 int pf_device_cus()
