@@ -303,8 +303,8 @@ static hipError_t set_launch(smc2_ctx* c, PFGroup& gr)
 // Autotuner: for every launch group, time each candidate (workgroup size, draw
 // schedule, persistent or one-filter-per-workgroup grid) on a sample of the group's
 // filters at the first iteration's parameters (prior draws) and keep the fastest. The group's
-// untuned size is a candidate too (the defaults for few filters are no powers of two and wider than
-// N_x), so the choice is never slower than the default on the sample.
+// untuned configuration is a candidate too (the defaults for few filters are no powers of two and
+// wider than N_x) and gives way only to one 2% faster, more than two timings of one differ by.
 // Results do not depend on the choice (every draw is a function of its coordinates),
 // only the time does. Leaves the sampler state as smc2_init found it (k = 0).
 static hipError_t autotune(smc2_ctx* c)
@@ -335,8 +335,8 @@ static hipError_t autotune(smc2_ctx* c)
         std::vector<int32_t> sample(S);
         for (int i = 0; i < S; ++i) sample[i] = host_items[gr.first_item + (int)((long)i * gr.n_items / S)];
         e = hipMemcpyAsync(d_tune, sample.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s);
-        PFGroup best = gr;
-        float best_ms = -1.f;
+        PFGroup best = gr, untuned = gr;
+        float best_ms = -1.f, untuned_ms = -1.f;
         const int full = ((gr.max_nx + 63) / 64) * 64;
         std::vector<int> sizes{gr.block};
         for (int b = 64; b <= std::min(full, 1024); b *= 2)
@@ -373,7 +373,10 @@ static hipError_t autotune(smc2_ctx* c)
                     a.prio_scale = prio_scale(cand, S);
                     int grid = pers ? std::min(cand.grid, S) : 0;
                     float ms = -1.f;
-                    for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // rep 0 warms up
+                    const bool is_untuned =
+                        b == gr.block && sc == gr.sched && pers == (gr.n_items > cand.resident ? 1 : 0);
+                    // rep 0 warms up; a candidate then half as slow again as the best is out
+                    for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
                         if (pers) e = hipMemsetAsync(d_queue, 0, sizeof(int32_t), s);
                         if (e == hipSuccess) e = hipEventRecord(t0, s);
                         if (e == hipSuccess) e = launch_pf(cfg.precision, cfg.model, cfg.obs, sc, b, lds, a, s, grid);
@@ -382,13 +385,23 @@ static hipError_t autotune(smc2_ctx* c)
                         float t = 0.f;
                         if (e == hipSuccess) e = hipEventElapsedTime(&t, t0, t1);
                         if (rep > 0 && (ms < 0.f || t < ms)) ms = t;
+                        if (rep == 0 && !is_untuned && best_ms >= 0.f && t > 1.5f * best_ms) break;
                     }
-                    if (e == hipSuccess && (best_ms < 0.f || ms < best_ms)) {
+                    if (e != hipSuccess || ms < 0.f) continue;
+                    if (best_ms < 0.f || ms < best_ms) {
                         best_ms = ms;
                         best = cand;
                     }
+                    if (is_untuned) {
+                        untuned_ms = ms;
+                        untuned = cand;
+                    }
                 }
             }
+        }
+        if (untuned_ms >= 0.f && best_ms > 0.98f * untuned_ms) {
+            best_ms = untuned_ms;
+            best = untuned;
         }
         if (e == hipSuccess && best_ms >= 0.f) {
             // the chosen size must hold every run of the group
