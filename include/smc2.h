@@ -117,8 +117,7 @@ extern "C" {
                                (Eq. l_weights). Iteration 1 draws from the prior. */
 
 /* particle-filter draw schedule (smc2_config.schedule); both give identical results */
-#define SMC2_SCHED_AUTO 0     /* per draw, except SIR/SEIR shapes where pooled is faster
-                                 (the score launches of SMC2_PROP_LANGEVIN: per draw)     */
+#define SMC2_SCHED_AUTO 0     /* per draw (the autotuner may choose the other)            */
 #define SMC2_SCHED_PER_DRAW 1 /* each lane takes its draws one after another; a wave
                                  settles those that its first attempts left open         */
 #define SMC2_SCHED_POOLED 2   /* SIR/SEIR: a wave pools its draws and runs the final
@@ -165,8 +164,10 @@ typedef struct {
     int32_t lkernel;   /* SMC2_L_FORWARD or SMC2_L_GAUSS_OPT                            */
     int32_t pf_always; /* 1: resample the particle filter at every step                 */
     int32_t use_graph; /* 1: replay each iteration as one captured HIP graph            */
-    int32_t block;     /* particle-filter workgroup size, a multiple of 64 up to 1024
-                          (0: chosen from the filter's LDS footprint)                   */
+    int32_t block;     /* particle-filter workgroup size, a multiple of 64 up to 1024 (0:
+                          chosen from the filter's LDS footprint and draws, the number of
+                          filters of its launch and the device's CUs; a filter that fits in
+                          LDS in any size is accepted)                                  */
     int32_t schedule;  /* SMC2_SCHED_*: particle-filter draw schedule (same results)     */
     double n_pop;      /* population size, integer, 1 .. 2^24 (not used by SMC2_LINGAUSS) */
     const double* prior;  /* host, D x 3 row-major: {family, a, b} per coordinate        */
@@ -175,8 +176,9 @@ typedef struct {
     int32_t n_fixed;
     int32_t tune;       /* 1: smc2_init times the candidate particle-filter launch
                            configurations (workgroup size, draw schedule, persistent grid)
-                           of every launch group on a sample of its filters and keeps the
-                           fastest; 0: defaults from the LDS footprint. Same results.     */
+                           of every launch group, the default among them, on a sample of its
+                           filters and keeps the default unless one is 2% faster; 0: the
+                           defaults. Same results.                                        */
     int32_t persistent; /* with tune = 0, SMC2_LAUNCH_*: how the filters are launched
                            (same results)                                                 */
     int32_t mlp_epochs; /* learned proposal: training epochs per iteration (0 .. 1000)     */

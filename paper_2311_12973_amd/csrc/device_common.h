@@ -102,8 +102,9 @@ __device__ __forceinline__ double normal_call(uint32_t c0, uint32_t c1, uint32_t
 // a / b correctly rounded, for positive normal operands whose quotient needs no range
 // scaling: a >= 2^-100, b in [2^-100, 2^100], a / b below 2^100. Then the scale steps of
 // the general division sequence leave the operands unchanged and its fix-up step passes
-// the value through, so the core below (reciprocal, Newton steps, quotient, residual
-// corrections, all FMAs) gives the same bits as the general division.
+// the value through, so the core below gives the same bits as the general division: Markstein's
+// scheme (IBM J. Res. Dev. 34, 1990), a reciprocal refined by Newton steps, the quotient and
+// its residual corrections, all FMAs.
 template <typename real> __device__ __forceinline__ real rdiv_inrange(real a, real b);
 template <> __device__ __forceinline__ float rdiv_inrange<float>(float a, float b)
 {
@@ -139,8 +140,8 @@ template <> __device__ __forceinline__ float rsqrt_inrange<float>(float x)
 }
 template <> __device__ __forceinline__ double rsqrt_inrange<double>(double x)
 {
-    // the coupled iteration for the root g and half its reciprocal h, then two residual
-    // corrections
+    // Goldschmidt's coupled iteration for the root g and half its reciprocal h, then two
+    // residual corrections
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
     const double r = fma(-h, g, 0.5);

@@ -68,9 +68,9 @@ constexpr size_t PF_LDS_MAX = 160 * 1024 - 256;
 
 // Dynamic LDS bytes of one filter workgroup.
 size_t pf_lds_bytes(int model, int prec, int block, int nx, int T, int sched);
-// The kernel variant to run for a requested draw schedule (PF_SCHED_AUTO: per draw, except
-// where the pooled one measured faster), with score = true its score-carrying form; -1 when
-// the pooled schedule was requested but cannot run, or the model has no score.
+// The kernel variant to run for a requested draw schedule (PF_SCHED_AUTO: per draw), with
+// score = true its score-carrying form; -1 when the pooled schedule was requested but cannot
+// run, or the model has no score.
 int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requested, bool score = false);
 // Default workgroup size for a filter of this shape (64 .. 1024 threads), in a launch of
 // n_filters filters of that shape (0: of several shapes) on a device of n_cu CUs.

@@ -501,7 +501,8 @@ extern "C" int smc2_init(const smc2_config* cfg, int32_t n_runs, const smc2_run*
         PFGroup gr{b, 0, (int)items.size(), 0, pooled_variant, cfg->persistent == SMC2_LAUNCH_PERSISTENT ? 1 : 0,
                    0, 0, 0, 0.f, 0.0, 0, 0.f};
         const size_t g0 = idx;
-        // the pooled schedule when every run of the group fits in LDS with it
+        // the variant of the requested schedule (pooled on request only); a run that the pooled
+        // one does not fit refuses the context
         for (size_t x = g0; x < run_order.size() && blk[run_order[x]] == b; ++x) {
             const int r = run_order[x];
             const int sc = pf_pick_schedule(cfg->model, cfg->precision, b, runs[r].n_x, runs[r].T, want, lgv);
