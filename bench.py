@@ -53,20 +53,22 @@ VALU_PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # rocprofv3 figures of the particle-filter kernel, per workload, measured on the kernel
 # sources and build flags with hash `sha` (profiles/<file>): VALU instructions executed by
 # active lanes per executed particle-step (SQ_INSTS_VALU x 64 x lane utilisation), HBM
-# bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated on a 256 MiB device copy) and the
-# VALU-busy fraction (SQ_ACTIVE_INST_VALU / 256 CUs / (GRBM_GUI_ACTIVE / 8 XCDs): cycles
-# in which the VALU issued, whatever the lanes; the counters' ratio reads up to 1.13 where issue
-# never pauses). A changed kernel reports them as null.
+# bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated on a 256 MiB device copy) and
+# valu_busy, the VALU instructions issued per CU and cycle (SQ_ACTIVE_INST_VALU / 256 CUs /
+# (GRBM_GUI_ACTIVE / 8 XCDs)), whatever their lanes. It is no fraction: measured with 16 waves
+# a CU and nothing else, a CU issues 1.36 moves, 1.26 FP32 FMAs, 1.15 three-input XORs, 1.03
+# XORs, 0.84 FP64 FMAs, 0.80 32-bit multiplies or 0.46 reciprocals a cycle, so the peak of one
+# above is a nominal rate that a mix can pass. A changed kernel reports them as null.
 KERNEL_SOURCES = ["paper_2311_12973_amd/csrc/pf_kernel.hip", "paper_2311_12973_amd/csrc/pf_kernel.h",
                   "paper_2311_12973_amd/csrc/device_common.h", "paper_2311_12973_amd/csrc/fast_fp64.h",
                   "paper_2311_12973_amd/csrc/block_ops.h",
                   "paper_2311_12973_amd/build.py"]
 MEASURED = {
-    "age_seir": dict(sha="c9bef2e7af3691b4", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=129687745,
-                     valu_busy=1.0254,
+    "age_seir": dict(sha="478a312766f593d0", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=129824850,
+                     valu_busy=1.0255,
                      profile="profiles/pf_kernel_age_seir_n16384_nx2048_t365.txt"),
-    "seir": dict(sha="c9bef2e7af3691b4", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1122831,
-                 valu_busy=1.1296,
+    "seir": dict(sha="478a312766f593d0", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1125592,
+                 valu_busy=1.1298,
                  profile="profiles/pf_kernel_seir_n1024_nx512_t100.txt"),
 }
 
