@@ -324,14 +324,20 @@ static hipError_t autotune(smc2_ctx* c)
     const std::vector<int32_t>& host_items = c->host_items;
     for (PFGroup& gr : c->groups) {
         if (e != hipSuccess) break;
-        // sample: about two resident waves of workgroups, strided over the cost-sorted list, or a group
-        // of up to twice as many whole (a narrower candidate may hold all of such a sample at once,
-        // but not all of the group)
+        // sample: about two rounds of resident workgroups, strided over the cost-sorted list; four where
+        // the group's filters differ in cost (over two the few longest set the time, which favours
+        // workgroups wider than the whole group wants); a group of up to twice as many whole (a
+        // narrower candidate may hold all of such a sample at once, but not all of the group)
         int per_cu = 1;
         e = pf_occupancy(cfg.precision, cfg.model, cfg.obs, gr.sched, gr.block, gr.lds, &per_cu);
         if (e != hipSuccess) break;
-        const int two = std::max(64, 2 * std::max(per_cu, 1) * std::max(c->n_cu, 1));
-        const int S = gr.n_items <= 2 * two ? gr.n_items : two;
+        const auto cost = [&](int item) {
+            const smc2_run& r = c->runs[host_items[item] / cfg.N];
+            return (int64_t)r.T * r.n_x;
+        };
+        const bool even = cost(gr.first_item) == cost(gr.first_item + gr.n_items - 1);
+        const int rounds = std::max(64, (even ? 2 : 4) * std::max(per_cu, 1) * std::max(c->n_cu, 1));
+        const int S = gr.n_items <= 2 * rounds ? gr.n_items : rounds;
         std::vector<int32_t> sample(S);
         for (int i = 0; i < S; ++i) sample[i] = host_items[gr.first_item + (int)((long)i * gr.n_items / S)];
         e = hipMemcpyAsync(d_tune, sample.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s);
