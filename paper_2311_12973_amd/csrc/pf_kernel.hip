@@ -1442,9 +1442,10 @@ static int pf_most_waves_block(int model, int prec, int nx, int T, int requested
 //    wide workgroups (600 linear-Gaussian filters, N_x = 1000, 200 days: three rounds of 1024
 //    threads 3.49 ms, one of 256 2.17; 2500, N_x = 512: 512 threads 1.05, 256 0.79).
 // Over 1955 launches per draw (the four models, SEIR and SIR in both precisions, SEIR and
-// linear-Gaussian with scores, 513 to 12288 filters on 256 CUs, N_x = 40 to 4096) the size taken is 0.4% slower
-// than the fastest of nine in the geometric mean, 3% at the 95th percentile and 16% at most; the
-// most resident waves alone 5%, 31% and 57%. Over 1225 pooled ones 1.6%, 12% and 32%; 6%, 31%, 54%.
+// linear-Gaussian with scores, 513 to 12288 filters on 256 CUs, N_x = 40 to 4096) the size taken is
+// 0.3% slower than the fastest of nine in the geometric mean, 2% at the 95th percentile and 16% at
+// most; the most resident waves alone 5%, 31% and 57%. Over 1225 pooled ones 1.4%, 12% and 32%; 6%,
+// 31% and 54%.
 static int pf_many_filters_block(int model, int prec, int nx, int T, int requested_sched, bool score, int n_filters,
                                  int n_cu)
 {
@@ -1452,7 +1453,8 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
     const int chunks = (nx + 63) / 64, items = day_items(model, nx), flows = items / chunks;
     const double day = model == MODEL_AGE ? 0.2 : 0.7;
     // 0: the size does not fit, or spreads draws over the waves of a full CU, which shortens a day but
-    // takes no work off it (4096 filters, N_x = 300, 60 days: 512 threads 4.84 ms, 128 3.83)
+    // takes no work off it (4096 filters, N_x = 300, 60 days: 512 threads 4.84 ms, 128 3.83; 2048 with
+    // scores, N_x = 64: 128 threads, eight workgroups a CU, 0.581, 64 0.535)
     const auto estimate = [&](int b) {
         const int w = b / 64, sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
         if (sc < 0) return 0.0;
@@ -1460,7 +1462,7 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
         if (lds > PF_LDS_MAX) return 0.0;
         const int per_cu = pf_resident(lds, w), round = n_cu * per_cu;
         const bool several = n_filters > round;
-        if (w > chunks && several) return 0.0;
+        if (w > chunks && (several || (n_filters + n_cu - 1) / n_cu * w >= 16)) return 0.0;
         const double mean = (double)chunks / w;
         const double passes = sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED ? (double)nx / b
                               : w > chunks ? (double)((items + w - 1) / w) / flows
