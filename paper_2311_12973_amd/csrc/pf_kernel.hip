@@ -1452,9 +1452,11 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
     static const int sizes[] = {64, 128, 192, 256, 512, 1024};
     const int chunks = (nx + 63) / 64, items = day_items(model, nx), flows = items / chunks;
     const double day = model == MODEL_AGE ? 0.2 : 0.7;
-    // 0: the size does not fit, or spreads draws over the waves of a full CU, which shortens a day but
-    // takes no work off it (4096 filters, N_x = 300, 60 days: 512 threads 4.84 ms, 128 3.83; 2048 with
-    // scores, N_x = 64: 128 threads, eight workgroups a CU, 0.581, 64 0.535)
+    // 0: the size does not fit, or spreads draws over more waves than a CU holds at once, which
+    // shortens a day but takes no work off it (4096 filters, N_x = 300, 60 days: 512 threads 4.84 ms,
+    // 128 3.83), or a single wave's, which never waits at a barrier, over those of a full CU (2048 with
+    // scores, N_x = 64: 128 threads, eight workgroups a CU, 0.577 ms, 64 0.535; but 1000 SIR filters,
+    // N_x = 100: four workgroups of 256 threads a CU 0.474, of 128 0.495)
     const auto estimate = [&](int b) {
         const int w = b / 64, sc = pf_pick_schedule(model, prec, b, nx, T, requested_sched, score);
         if (sc < 0) return 0.0;
@@ -1462,7 +1464,8 @@ static int pf_many_filters_block(int model, int prec, int nx, int T, int request
         if (lds > PF_LDS_MAX) return 0.0;
         const int per_cu = pf_resident(lds, w), round = n_cu * per_cu;
         const bool several = n_filters > round;
-        if (w > chunks && (several || (n_filters + n_cu - 1) / n_cu * w >= 16)) return 0.0;
+        const bool full_cu = (n_filters + n_cu - 1) / n_cu * w >= 16;
+        if (w > chunks && (several || (chunks == 1 && full_cu))) return 0.0;
         const double mean = (double)chunks / w;
         const double passes = sc == PF_SCHED_POOLED || sc == PF_SCHED_SCORE_POOLED ? (double)nx / b
                               : w > chunks ? (double)((items + w - 1) / w) / flows

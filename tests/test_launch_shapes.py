@@ -48,8 +48,9 @@ def _default_block(model, prec, nx, T, n_filters, schedule=G.SCHED_AUTO, score=F
     # sizes other than the most resident waves'
     (G.SEIR, G.PREC_FP32, False, 4096, 128, 60, 64), (G.SEIR, G.PREC_FP32, False, 3000, 257, 60, 64),
     (G.SEIR, G.PREC_FP32, False, 513, 40, 60, 192), (G.SIR, G.PREC_FP32, False, 600, 100, 60, 256),
-    # draws spread only while the CU has a wave slot free
-    (G.SEIR, G.PREC_FP32, True, 2048, 64, 60, 64), (G.SEIR, G.PREC_FP64, False, 2000, 64, 60, 64)])
+    # a single wave's draws spread only while the CU has a wave slot free
+    (G.SEIR, G.PREC_FP32, True, 2048, 64, 60, 64), (G.SEIR, G.PREC_FP64, False, 2000, 64, 60, 64),
+    (G.SIR, G.PREC_FP32, False, 1000, 100, 60, 256)])
 def test_many_filters_take_the_size_that_measured_fastest(model, prec, score, n, nx, T, fastest):
     """Shapes where the sizes' times lie far apart (10% to 60%): the fastest of those measured."""
     assert _default_block(model, prec, nx, T, n, score=score) == fastest
