@@ -64,11 +64,11 @@ KERNEL_SOURCES = ["paper_2311_12973_amd/csrc/pf_kernel.hip", "paper_2311_12973_a
                   "paper_2311_12973_amd/csrc/block_ops.h",
                   "paper_2311_12973_amd/build.py"]
 MEASURED = {
-    "age_seir": dict(sha="b2e9843b1fa2981f", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=130004870,
-                     valu_busy=1.0255,
+    "age_seir": dict(sha="e4593080e33dc1e6", valu_lane_instr_per_pstep=1805.1, hbm_bytes_per_launch=129603749,
+                     valu_busy=1.0251,
                      profile="profiles/pf_kernel_age_seir_n16384_nx2048_t365.txt"),
-    "seir": dict(sha="b2e9843b1fa2981f", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1125567,
-                 valu_busy=1.1291,
+    "seir": dict(sha="e4593080e33dc1e6", valu_lane_instr_per_pstep=1038.9, hbm_bytes_per_launch=1125595,
+                 valu_busy=1.1278,
                  profile="profiles/pf_kernel_seir_n1024_nx512_t100.txt"),
 }
 
