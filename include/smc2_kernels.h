@@ -117,7 +117,7 @@ int smc2_pf_trace_state(const smc2_config* cfg, int32_t n_theta, const double* d
  * vanish gets -inf and a zero score. The scores sit in LDS beside the counts. Draw
  * schedule: per draw (SMC2_SCHED_AUTO or SMC2_SCHED_PER_DRAW; n_x up to 2048, for SEIR
  * in FP64 with T <= 365) or pooled (SMC2_SCHED_POOLED, SIR and SEIR, n_x up to about
- * 1024 with the scores; faster only for small filters), the same bits either way. A
+ * 1024 with the scores; slower at the shapes measured), the same bits either way. A
  * schedule that does not fit returns SMC2_E_ARG. The workspace is
  * smc2_pf_workspace_bytes'. Returns after the stream has run the filters. */
 int smc2_pf_score(const smc2_config* cfg, int32_t n_theta, const double* d_theta, const smc2_run* run, uint32_t k,

@@ -1529,9 +1529,9 @@ int pf_pick_schedule(int model, int prec, int block, int nx, int T, int requeste
         const bool ok = (model == MODEL_SIR || model == MODEL_SEIR) &&
                         pf_lds_bytes(model, prec, block, nx, T, PF_SCHED_SCORE_POOLED) <= PF_LDS_MAX;
         // automatic: the per-draw form. The pooled one's extra LDS (the wave pools beside
-        // the score words) leaves fewer workgroups per CU, and it measured slower at the
-        // SEIR shapes (3.43 against 4.13 ms at N_x = 512, 43.7 against 52.3 ms at N_x =
-        // 1024); it is faster for small launch-bound filters, where the autotuner finds it
+        // the score words) leaves fewer workgroups per CU, and a Langevin iteration with it is
+        // slower (SEIR, 1024 filters, N_x = 512, 3.39 against 2.18 ms; 4096, N_x = 1024, 38.5
+        // against 26.6 ms; SIR, 64 filters, N_x = 64, 0.42 against 0.37 ms)
         if (requested == PF_SCHED_POOLED) return ok ? PF_SCHED_SCORE_POOLED : -1;
         return PF_SCHED_SCORE;
     }
